@@ -343,6 +343,7 @@ struct SetupArgs {
   int taps_stride;          // rows between sequences in taps (0: packed)
   int K;
   int max_new;              // per-sequence bound on new rows
+  int rows;                 // host bound on the rows of the pass
   int V_T;
   int32_t* slot_len;
   int32_t* pend_n;

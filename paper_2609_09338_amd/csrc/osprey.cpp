@@ -1192,6 +1192,7 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
   sa.taps_stride = a->taps_stride;
   sa.K = K;
   sa.max_new = pending ? c.max_k + 1 : std::max(max_new, 1);
+  sa.rows = (int)rows;
   sa.V_T = c.vocab_target;
   sa.slot_len = W.slot_len;
   sa.pend_n = W.pend_n;

@@ -1,0 +1,93 @@
+"""Prompts and further turns on the GPU against the oracle: passes of many new rows per
+sequence (the tiled products, attention by blocks of query vectors, the row setup), at
+the sizes where their tiles and context splits begin and end."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import harness as OH
+
+pytestmark = pytest.mark.gpu
+
+# name -> body, head dim and group; rows per sequence over each cached context.  A block
+# holds 64 or 128 query vectors (rows x group), a step 64 positions, a product tile 128 rows.
+CASES = {
+    "group2_hd64": ("p_qwen_small", [(0, 9), (0, 33), (47, 64)]),
+    "group2_hd64_ragged": ("p_qwen_small", [(0, 128), (129, 1), (16, 200)]),
+    "group4_hd64_one": ("p_single64", [(300, 37)]),
+    "group2_hd128": ("p_single128", [(0, 129)]),
+    "group2_hd128_turn": ("p_single128", [(1000, 65)]),
+    "group4_hd128": ("p_inject", [(0, 70), (511, 17)]),
+    "wide_taps": ("p_wide_taps", [(0, 65), (3, 2), (64, 63)]),
+    "f32": ("p_tiny_f32", [(0, 65)]),
+    "f32_turn": ("p_tiny_f32", [(70, 3)]),
+}
+
+
+@pytest.mark.parametrize("K", [0, 3])
+@pytest.mark.parametrize("name", list(CASES))
+def test_prompt_matches_oracle(name, K):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import _lib as L
+    from paper_2609_09338_amd import workload as WL
+    from paper_2609_09338_amd.binding import Drafter, make_config
+    body, seqs = CASES[name]
+    w = synth.get(body)
+    w = w.with_(name="prompt_" + name, batch=len(seqs), K=max(K, 1), temps=(0.0,), draft_temps=())
+    weights, d2t = synth.make_weights(w), synth.make_d2t(w)
+    dr_o = OH.build_drafter(w, weights, d2t)
+    ctx, rows = [c for c, _ in seqs], [n for _, n in seqs]
+    blocks = synth.block_ids(w, [synth.blocks_needed(w, c + n + K + 1) for c, n in seqs])
+    cfg = make_config(n_layers=w.n_layers, d_model=w.d_model, n_q_heads=w.n_q_heads, n_kv_heads=w.n_kv_heads,
+                      head_dim=w.head_dim, d_ffn=w.d_ffn, vocab_draft=w.vocab_draft, vocab_target=w.vocab_target,
+                      target_hidden=w.target_hidden, n_taps=w.n_taps,
+                      dtype=L.OSPREY_BF16 if w.dtype == "bf16" else L.OSPREY_F32, qk_norm=w.qk_norm,
+                      rms_eps=w.rms_eps, rope_theta=w.rope_theta, max_batch=w.batch, max_k=3,
+                      max_seq_len=max(c + n for c, n in seqs) + K + 1, kv_num_blocks=sum(map(len, blocks)),
+                      max_new_rows=max(sum(rows), 1))
+    dev = "cuda:0"
+    dr = Drafter(cfg, {k: WL.to_dev(v, w, dev) for k, v in weights.items()}, torch.from_numpy(d2t).to(dev))
+    dr.kv.fill_(0xFF)          # unwritten cache memory is NaN: nothing may read it
+    toks, taps, ref, caches = [], [], [], []
+    for b, (c, n) in enumerate(seqs):
+        dr.seq_reset(b, blocks[b])
+        seq = OH.Sequence(w, c + n + K + 1)
+        if c:
+            k, v = synth.context_kv(w, b, c)
+            dr.kv_append(b, WL.to_dev(k, w, dev), WL.to_dev(v, w, dev))
+            seq.k[:, :c], seq.v[:, :c], seq.length = k, v, c
+        t, tp = synth.prompt_tokens(w, b, n), synth.taps(w, 0, b, n)
+        toks.append(t)
+        taps.append(tp)
+        ref.append(dr_o.draft(seq, t, tp, K, 0.0, np.zeros(max(K, 1))))
+        caches.append(seq)
+    logits = torch.empty((w.batch, max(K, 1), w.vocab_draft), device=dev)
+    drafts = torch.empty((w.batch, max(K, 1)), dtype=torch.int32, device=dev)
+    print(f"[prompt] {name} K {K}", flush=True)
+    dr.draft_step(list(range(w.batch)), K, WL.to_dev(np.concatenate(taps), w, dev), torch.zeros(w.batch, device=dev),
+                  n_new=rows, new_tokens=torch.from_numpy(np.concatenate(toks).astype(np.int32)).to(dev),
+                  draft_tokens=drafts if K else None, draft_logits=logits if K else None)
+    torch.cuda.synchronize()
+    assert dr.device_errors() == 0
+    kv = dr.kv.view(torch.bfloat16 if w.dtype == "bf16" else torch.float32).float().cpu().numpy()
+    kv = kv.reshape(cfg.kv_num_blocks, w.n_layers, 2, w.n_kv_heads, 16 * w.head_dim)
+    # stored values: half a bf16 ulp (2^-9 of the value) plus the 2e-2 that the parity tests
+    # allow a logit, at the size of a key or value; fp32 as its logits, 1e-4
+    rel, tol = (2.0 ** -8, 2e-2) if w.dtype == "bf16" else (0.0, 1e-4)
+    for b, (c, n) in enumerate(seqs):
+        assert dr.seq_length(b) == c + n
+        for j, cache in enumerate((caches[b].k, caches[b].v)):
+            pages = kv[blocks[b], :, j].reshape(len(blocks[b]), w.n_layers, w.n_kv_heads, *((16, w.head_dim) if j == 0 else (w.head_dim, 16)))
+            got = pages if j == 0 else pages.swapaxes(-1, -2)
+            got = got.transpose(1, 0, 3, 2, 4).reshape(w.n_layers, -1, w.n_kv_heads, w.head_dim)[:, c:c + n]
+            want = cache[:, c:c + n]
+            assert np.all(np.abs(got - want) <= rel * np.abs(want) + tol)
+        if K:
+            _, lo, _, _ = ref[b]
+            g = logits[b].cpu().numpy()
+            m = np.isfinite(lo)
+            assert np.array_equal(m, np.isfinite(g))
+            assert np.max(np.abs(g[m] - lo[m])) < tol
+            assert drafts[b].cpu().tolist() == ref[b][0].tolist()
