@@ -277,6 +277,7 @@ struct AttnArgs {
   const float* q_prep;      // [rows][nq][hd] queries already normalised, rotated and scaled, with
                             // the new keys/values already in the cache (nullable: done here)
   float* part;              // [rows][nq][n_split][hd + 2]
+  int direct;               // attention over rows: one split, written to o_hi / o_lo without a merge
   float* o;                 // [rows][nq*hd]
   uint16_t* o_hi;           // matrix-core path: o as bf16 hi / lo pairs instead (nullable)
   uint16_t* o_lo;
@@ -294,6 +295,13 @@ struct AttnArgs {
   int tree_slots;           // slots of tree_kv
 };
 void launch_attention(int kvdtype, const AttnArgs& a, hipStream_t st);
+// The same for passes of many query vectors per sequence (bf16 caches; a.q_prep set, a.cu
+// groups the rows, whose positions ascend within a sequence): blocks of query vectors, each
+// walking its pages once.  attn_rows_tiles: blocks per kv head and split of one sequence of
+// `rows_per_seq` rows whose kv heads serve `group` query heads.
+bool attn_rows_supported(int kvdtype, int rows_per_seq, int group);
+int attn_rows_tiles(int rows_per_seq, int group);
+void launch_attention_rows(const AttnArgs& a, hipStream_t st);
 // Matrix-core path: per row, sum the QKV split partials, normalise and rotate q
 // and k, write q * (1/sqrt(hd)) to q_out and the new k, v into the cache.
 void launch_rows_qkv(int kvdtype, const AttnArgs& a, float* q_out, hipStream_t st);

@@ -396,15 +396,37 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
   return p;
 }
 
+// Context splits of a pass whose attention runs by blocks of query vectors: none while
+// the tiles of vectors give the chip two blocks per CU by themselves; else as many pieces
+// of at least kRowSplitLen positions as reach that.
+constexpr long kRowSplitLen = 128;
+SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, int rows_per_seq, int rows,
+                          int max_split) {
+  const osprey_config& c = h->cfg;
+  const int group = c.n_q_heads / c.n_kv_heads;
+  const long ctx = (long)sp.n_split * sp.split_len;   // at least the longest context
+  // a batch's tiles: the longest sequence's, and no more than its rows fill
+  const int per_seq = attn_rows_tiles(rows_per_seq, group);
+  const long tiles = std::min<long>((long)B * per_seq, (long)attn_rows_tiles(rows, group) + B);
+  long n = 2L * h->n_cu / (tiles * c.n_kv_heads);
+  n = std::max<long>(1, std::min<long>(std::min<long>(n, max_split), ctx / kRowSplitLen));
+  SplitPlan p = sp;
+  long len = ((ctx + n - 1) / n + 63) / 64 * 64;
+  p.split_len = (int)len;
+  p.n_split = (int)((ctx + len - 1) / len);
+  return p;
+}
+
 // Attention over the cache and the merge of its context splits.  Timed (family 1),
 // the pair runs kTimedRepeats times back to back between the events: it is idempotent
 // (a new row's keys and values are written again with the same values, every output is
 // overwritten), so the events' own overhead is shared by as many launches.
-void run_attention(osprey_handle* h, const AttnArgs& a, bool merge = true) {
+void run_attention(osprey_handle* h, const AttnArgs& a, bool merge = true, bool rows = false) {
   const int t = h->t_begin(1);
   const int reps = t >= 0 ? kTimedRepeats : 1;
   for (int rep = 0; rep < reps; ++rep) {
-    launch_attention(h->cfg.dtype, a, h->stream);
+    if (rows) launch_attention_rows(a, h->stream);
+    else launch_attention(h->cfg.dtype, a, h->stream);
     if (merge) launch_attn_combine(a, h->stream);
   }
   h->t_end(t, reps);
@@ -678,13 +700,22 @@ void run_body_mr(osprey_handle* h, const RowMeta& rows, const int32_t* cu, int B
       launch_rows_qkv(c.dtype, a, W.o, h->stream);
       a.q_prep = W.o;
     }
+    // Sequences of more than 16 prepared query vectors per kv head walk their pages once per
+    // block of vectors instead of once per 16 vectors (attention_rows.hip).
+    const bool by_rows = a.q_prep && attn_rows_supported(c.dtype, rows_per_seq, nq / nkv);
+    if (by_rows) {
+      const SplitPlan rp = plan_row_splits(h, sp, B, rows_per_seq, rows.max_rows, tree ? kMaxSplit - 1 : kMaxSplit);
+      a.n_split = rp.n_split;
+      a.split_len = rp.split_len;
+      a.direct = rp.n_split == 1 && !tree;
+    }
     // Passes that are not tree passes and have at most kAttnMergeMaxSplit splits merge
     // the context splits while the O projection stages its inputs (one launch fewer per
     // layer); otherwise the merge kernel writes o as the projection's input pairs.  (At
     // 32-64 rows each O block reads its inputs' bytes once per split: with 1024-position
     // splits c4 / c5 gained nothing, with 2048 (at most 3-5 splits) c5 3.168 -> 3.151 ms.)
-    const bool merge_in_o = skinny && !tree && sp.n_split <= kAttnMergeMaxSplit;
-    run_attention(h, a, !merge_in_o);
+    const bool merge_in_o = skinny && !tree && !a.direct && a.n_split <= kAttnMergeMaxSplit;
+    run_attention(h, a, !merge_in_o && !a.direct, by_rows);
     // O projection; residual + post-attention RMSNorm
     GemvArgs go = gb;
     go.ld_xa = nq * hd;
@@ -697,8 +728,8 @@ void run_body_mr(osprey_handle* h, const RowMeta& rows, const int32_t* cu, int B
     if (merge_in_o) {
       go.attn_part = W.attn_part;
       go.attn_pos = rows.pos;
-      go.attn_nsplit = sp.n_split;
-      go.attn_split_len = sp.split_len;
+      go.attn_nsplit = a.n_split;
+      go.attn_split_len = a.split_len;
       go.attn_hd = hd;
       rn.ks = gemm(SRC_ATTN, EPI_STORE, go);
     } else {
