@@ -20,7 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libosprey.so")
 SOURCES = ["gemv.hip", "gemv_taps.hip", "gemv_qkv.hip", "gemv_resid.hip", "gemv_swiglu.hip",
-           "gemv_logits.hip", "gemm_mfma.hip", "skinny.hip", "rows.hip", "attention.hip", "attention_rows.hip", "sample.hip", "verify.hip", "verify_static.hip",
+           "gemv_logits.hip", "gemm_mfma.hip", "gemm_rows.hip", "skinny.hip", "rows.hip", "attention.hip", "attention_rows.hip", "sample.hip", "verify.hip", "verify_static.hip",
            "state.hip", "tree.hip", "osprey.cpp"]
 ARCH = "gfx950"
 

@@ -125,23 +125,23 @@ constexpr int kMaxSplitAttn = 64;   // context splits per row (bound; the host k
 // (in split order) on the matrix-core path, else the plain row.  Every split's load of
 // every element is requested at once, from a clamped address (loads past the last
 // split re-read it and add zero), so no load waits on a condition.
-template <int N>
+template <int N, int Q = kMaxKSplit>
 OSP_DEV void qkv_get(const AttnArgs& a, const long (&off)[N], float (&out)[N]) {
   if (a.qkv_ks <= 1) {
 #pragma unroll
     for (int j = 0; j < N; ++j) out[j] = a.qkv[off[j]];
     return;
   }
-  float v[N][kMaxKSplit];
+  float v[N][Q];
 #pragma unroll
-  for (int k = 0; k < kMaxKSplit; ++k)
+  for (int k = 0; k < Q; ++k)
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j][k] = a.qkv[min(k, a.qkv_ks - 1) * a.qkv_split + off[j]];
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     float s = 0.f;
 #pragma unroll
-    for (int k = 0; k < kMaxKSplit; ++k) s += k < a.qkv_ks ? v[j][k] : 0.f;
+    for (int k = 0; k < Q; ++k) s += k < a.qkv_ks ? v[j][k] : 0.f;
     out[j] = s;
   }
 }
@@ -167,7 +167,7 @@ OSP_DEV float qkv_at(const AttnArgs& a, long off) {
 template <typename TKV, int HD>
 constexpr bool kBatchQkv = HD == 128 && sizeof(TKV) == 2;
 
-template <int HD, bool BATCH, int N>
+template <int HD, bool BATCH, int N, bool FEW = false>
 OSP_DEV void qkv_lanes(const AttnArgs& a, const long (&base)[N], int lane, float (&out)[2 * N]) {
   constexpr int HALF = HD / 2;
 #pragma unroll
@@ -177,7 +177,9 @@ OSP_DEV void qkv_lanes(const AttnArgs& a, const long (&base)[N], int lane, float
     long off[2 * N];
 #pragma unroll
     for (int j = 0; j < N; ++j) { off[2 * j] = base[j] + lane; off[2 * j + 1] = base[j] + lane + HALF; }
-    qkv_get<2 * N>(a, off, out);
+    // (large passes split K little: four loads cover their splits)
+    if (FEW && a.qkv_ks <= 4) qkv_get<2 * N, 4>(a, off, out);
+    else qkv_get<2 * N>(a, off, out);
   } else {
 #pragma unroll
     for (int j = 0; j < N; ++j) { out[2 * j] = qkv_at(a, base[j] + lane); out[2 * j + 1] = qkv_at(a, base[j] + lane + HALF); }
@@ -702,7 +704,7 @@ __global__ void __launch_bounds__(256) k_rows_qkv(AttnArgs a, float* q_out) {
   if (hh < a.nq) {
     const long qo = (long)r * a.qkv_w + (long)hh * HD;
     float qv[2];
-    qkv_lanes<HD, true>(a, {qo}, lane, qv);
+    qkv_lanes<HD, true, 1, true>(a, {qo}, lane, qv);
     float q1 = qv[0], q2 = qv[1];
     norm_rope<TKV, HD>(a, a.q_norm, pos, lane, q1, q2);
     if (lane < HALF) {
@@ -716,7 +718,7 @@ __global__ void __launch_bounds__(256) k_rows_qkv(AttnArgs a, float* q_out) {
   const long ko = (long)r * a.qkv_w + (long)(a.nq + g) * HD;
   const long vo = (long)r * a.qkv_w + (long)(a.nq + a.nkv + g) * HD;
   float kv[4];
-  qkv_lanes<HD, true>(a, {ko, vo}, lane, kv);
+  qkv_lanes<HD, true, 2, true>(a, {ko, vo}, lane, kv);
   float k1 = kv[0], k2 = kv[1];
   const float v1 = kv[2], v2 = kv[3];
   norm_rope<TKV, HD>(a, a.k_norm, pos, lane, k1, k2);

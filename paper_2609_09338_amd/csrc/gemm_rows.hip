@@ -1,0 +1,238 @@
+// Tiled matrix-core products for passes of more than 64 rows (prompts, large batches):
+// Y[r][n] = sum_c X[r][c] W[n][c], bf16 weights, X as bf16 hi / lo pairs (taps: bf16).
+//
+// The kernel of gemm_mfma.h gives every 64 rows a block of their own, whose weights go
+// straight from memory to registers, and splits K into 256-column pieces whatever the
+// size: at thousands of rows each weight is read once per 64 rows and 8-16 partial sums
+// of every output pass through memory.  Here a block computes 128 rows x 256 weight rows
+// (a wavefront 64 x 128), and K is split only as far as it takes to give every CU two
+// blocks.  Per 32 columns a block copies 16 KB of inputs (hi, lo) and 16 KB of weights
+// straight into LDS (buffer loads to LDS, no registers) while it multiplies the 32
+// columns before; a wavefront reads 16 fragments from LDS for 64 products, about half of
+// what the LDS delivers in that time.  Two blocks per CU (64 KB of LDS, 2 wavefronts per
+// SIMD) cover each other's barriers.  16-byte pieces are permuted within a row by the
+// row, so that the 16 rows of a fragment read fall into different banks.
+//
+// The weights are the A operand, so a lane ends with four consecutive output columns of
+// one row: float4 stores of partial sums, and for gate/up (a wavefront holds the gate and
+// the up tile of the same columns) silu(g) u in registers, written as the down
+// projection's hi / lo input without the row kernel and its 2 x 2 F floats per row.
+// Blocks go to the XCDs in contiguous ranges of tiles, eight row tiles by rising weight
+// tile, so that an XCD's blocks share inputs and weights in its L2.
+// Bound by the matrix cores (two products per weight: hi and lo inputs).  Measured, before
+// and after: gate/up of 8200 rows (2 x 9728 x 2560) 4256 us and 1358 us of SwiGLU rows ->
+// 1325 us (1.23 PFLOP/s of products; a large library bf16 product reaches 1.22 on this
+// card), QKV (6144 x 5120) 2435 -> 939 us, taps (2560 x 12288) 2226 -> 599 us; 1999 rows
+// of the 1024-wide body: QKV 176 -> 60, gate/up 114 + 32 -> 59, down 66 -> 39, taps 226 -> 69.
+#include "common.h"
+#include "internal.h"
+
+#include <algorithm>
+
+namespace osp {
+
+typedef __bf16 gr_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float gr_f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned gr_u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kGrM = 128;        // input rows per block
+constexpr int kGrN = 256;        // weight rows per block
+constexpr int kGrK = 32;         // columns per step
+constexpr int kGrP = kGrK / 8;   // 16-byte pieces per row and step
+constexpr int kGrGroup = 8;      // row tiles walked together
+constexpr int kGrXcd = 8;
+
+// Where piece c of row r of a tile lies: four pieces per 64-byte row, permuted so that the
+// same piece of eight consecutive rows covers every bank once.
+OSP_DEV int gr_slot(int r, int c) { return r * kGrP + (c ^ ((r >> 1) & 3)); }
+
+OSP_DEV void gr_copy(const void* base, gr_u32x4* lds, int voffset, int soffset) {
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, voffset, soffset,
+                                           0, 0);
+}
+
+template <int SRC, int EPI>
+__global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt, int ks, int steps_per_split,
+                                                      int fused) {
+  constexpr bool EXACT_X = SRC == SRC_TAPS;   // inputs already bf16: no lo part
+  constexpr int XT = kGrM * kGrP;             // pieces of one input tile
+  constexpr int ST = (EXACT_X ? 1 : 2) * XT + kGrN * kGrP;
+  __shared__ __attribute__((aligned(16))) gr_u32x4 st0[ST];
+  __shared__ __attribute__((aligned(16))) gr_u32x4 st1[ST];
+
+  // ---- this block's tile ------------------------------------------------------------------
+  const int tiles = mt * nt, per = (tiles * ks + kGrXcd - 1) / kGrXcd;
+  const int id = (int)(blockIdx.x % kGrXcd) * per + (int)(blockIdx.x / kGrXcd);
+  if (id >= tiles * ks) return;
+  const int split = id / tiles, t = id % tiles;
+  const int g0 = t / (kGrGroup * nt) * kGrGroup, gm = min(kGrGroup, mt - g0);
+  const int tg = t - g0 * nt;
+  const int m0 = (g0 + tg % gm) * kGrM, nb = tg / gm;
+  const int rows = a.count ? min(*a.count, a.max_rows) : a.max_rows;
+  if (m0 >= rows) return;
+  const int n0 = nb * (EPI == EPI_SWIGLU ? kGrN / 2 : kGrN);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row = lane & 15, grp = lane >> 4;
+  const int k_beg = split * steps_per_split;
+  const int steps = min(steps_per_split, a.Kd / kGrK - k_beg);
+
+  // ---- copies: an instruction fills 16 rows (64 bytes each); a wavefront brings 32 input
+  //      rows and 64 weight rows of every step.  Rows past the end repeat the last one ---------
+  const int cr = lane >> 2;                  // row within an instruction's 16
+  int xo[2], wo[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = (wave * 2 + i) * 16 + cr;  // row of the tile
+    const int m = min(m0 + r, rows - 1);
+    const long ld = SRC == SRC_TAPS ? a.ldt : a.ld_xa;
+    const long src = SRC == SRC_TAPS ? a.tap_row[m] : m;
+    xo[i] = (int)(src * ld * 2) + (((lane & 3) ^ ((r >> 1) & 3)) * 16);
+  }
+  // gate/up: wavefronts 0 and 2 bring gate rows, 1 and 3 the up rows of the same columns
+  const void* wbase = (EPI == EPI_SWIGLU && (wave & 1)) ? a.w1 : a.w0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = i * 16 + cr;
+    const int n = min(n0 + (EPI == EPI_SWIGLU ? (wave >> 1) * 64 : wave * 64) + r, a.N - 1);
+    wo[i] = (int)((long)n * a.Kd * 2) + (((lane & 3) ^ ((r >> 1) & 3)) * 16);
+  }
+  auto copy_step = [&](gr_u32x4* st, int k) {
+    const int col = (k_beg + k) * kGrK;
+    if constexpr (SRC == SRC_TAPS) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) gr_copy(a.taps, st + (wave * 2 + i) * 64, xo[i], col * 2);
+    } else {
+      const bool s = col < a.seg;            // (segments are whole steps)
+      const void* xh = s ? a.xs_hi : a.xa_hi;
+      const void* xl = s ? a.xs_lo : a.xa_lo;
+      const int so = (s ? col : col - a.seg) * 2;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        gr_copy(xh, st + (wave * 2 + i) * 64, xo[i], so);
+        gr_copy(xl, st + XT + (wave * 2 + i) * 64, xo[i], so);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) gr_copy(wbase, st + (ST - kGrN * kGrP) + (wave * 4 + i) * 64, wo[i], col * 2);
+  };
+
+  // ---- products: wavefront (wm, wn) computes rows 64 wm .., weight rows 128 wn .. -----------
+  const int wm = wave & 1, wn = wave >> 1;
+  const bool work = m0 + wm * 64 < rows;
+  gr_f32x4 acc[8][4];
+#pragma unroll
+  for (int n = 0; n < 8; ++n)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[n][m] = gr_f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const gr_u32x4* st) {
+    if (!work) return;
+    gr_bf16x8 xh[4], xl[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int s = gr_slot(wm * 64 + 16 * m + row, grp);
+      xh[m] = __builtin_bit_cast(gr_bf16x8, st[s]);
+      if constexpr (!EXACT_X) xl[m] = __builtin_bit_cast(gr_bf16x8, st[XT + s]);
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const gr_bf16x8 w =
+          __builtin_bit_cast(gr_bf16x8, st[(ST - kGrN * kGrP) + gr_slot(wn * 128 + 16 * n + row, grp)]);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, xh[m], acc[n][m], 0, 0, 0);
+      if constexpr (!EXACT_X)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, xl[m], acc[n][m], 0, 0, 0);
+    }
+  };
+
+  // ---- two stages: one fills while the other is multiplied (the barrier waits for the
+  //      copies); the stages are arrays of their own, so that reads of one do not wait for
+  //      the copies into the other ----------------------------------------------------------
+  copy_step(st0, 0);
+  __syncthreads();
+  for (int k = 0; k < steps; k += 2) {
+    if (k + 1 < steps) copy_step(st1, k + 1);
+    compute(st0);
+    __syncthreads();
+    if (k + 1 >= steps) break;
+    if (k + 2 < steps) copy_step(st0, k + 2);
+    compute(st1);
+    __syncthreads();
+  }
+
+  // ---- lane holds Y[row 16 m + lane % 16][columns 16 n + 4 (lane / 16) .. + 4) ---------------
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const int r = m0 + wm * 64 + 16 * m + row;
+    if (r >= rows) continue;
+    if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int f = n0 + wn * 64 + 16 * i + 4 * grp;
+        if (f >= a.N) continue;
+        const gr_f32x4 g = acc[i][m], u = acc[4 + i][m];
+        if (fused) {
+          float y[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = g[e] / (1.0f + __expf(-g[e])) * u[e];
+          uint32_t h[2], l[2];
+          split_bf16x2(y[0], y[1], h[0], l[0]);
+          split_bf16x2(y[2], y[3], h[1], l[1]);
+          *reinterpret_cast<uint2*>(a.act_hi + (long)r * a.N + f) = make_uint2(h[0], h[1]);
+          *reinterpret_cast<uint2*>(a.act_lo + (long)r * a.N + f) = make_uint2(l[0], l[1]);
+        } else {
+          float* p = a.split_buf + ((long)split * a.max_rows + r) * 2 * a.N + f;
+          *reinterpret_cast<gr_f32x4*>(p) = g;
+          *reinterpret_cast<gr_f32x4*>(p + a.N) = u;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        const int c = n0 + wn * 128 + 16 * n + 4 * grp;
+        if (c < a.N) *reinterpret_cast<gr_f32x4*>(a.split_buf + ((long)split * a.max_rows + r) * a.N + c) = acc[n][m];
+      }
+    }
+  }
+}
+
+// K splits: as many as it takes to give 256 CUs two blocks each, of at least four steps.
+static int gemm_rows_splits(int tiles, int Kd, int& steps_per_split) {
+  const int steps = Kd / kGrK;
+  int ks = std::max(1, std::min(std::min(512 / tiles, steps / 4), kMaxKSplit));
+  steps_per_split = (steps + ks - 1) / ks;
+  return (steps + steps_per_split - 1) / steps_per_split;
+}
+
+// Passes of more than 128 rows (below, one 128-row tile leaves a wavefront pair idle and
+// too few blocks: at 96 rows of width 1024 the products took 11.7-13.2 us against
+// 11.3-12.1); whole 32-column steps, inputs and weights within the 2 GB a buffer offset reaches, and
+// rows of equal stride in both input segments; other shapes keep the kernel of gemm_mfma.h.
+bool gemm_rows_supported(SrcKind src, const GemvArgs& a, long input_rows) {
+  const long ld = src == SRC_TAPS ? a.ldt : a.ld_xa;
+  return (src == SRC_TAPS || src == SRC_PREP) && a.max_rows > kGrM && a.Kd % kGrK == 0 && a.seg % kGrK == 0 && a.N % 4 == 0 && !a.gather &&
+         (a.seg == 0 || a.ld_xs == a.ld_xa) && input_rows * ld * 2 < (1L << 31) && (long)a.N * a.Kd * 2 < (1L << 31);
+}
+
+template <int SRC, int EPI>
+static int launch_t(const GemvArgs& a, hipStream_t st) {
+  const int mt = (a.max_rows + kGrM - 1) / kGrM;
+  const int per = EPI == EPI_SWIGLU ? kGrN / 2 : kGrN;
+  const int nt = (a.N + per - 1) / per;
+  int sps = 0;
+  const int ks = gemm_rows_splits(mt * nt, a.Kd, sps);
+  const int grid = (mt * nt * ks + kGrXcd - 1) / kGrXcd * kGrXcd;
+  const int fused = EPI == EPI_SWIGLU && ks == 1 && a.act_hi;
+  hipLaunchKernelGGL((k_gemm_rows<SRC, EPI>), dim3(grid), dim3(256), 0, st, a, mt, nt, ks, sps, fused);
+  return fused ? 0 : ks;
+}
+
+int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st) {
+  if (src == SRC_TAPS) return launch_t<SRC_TAPS, EPI_STORE>(a, st);
+  if (epi == EPI_SWIGLU) return launch_t<SRC_PREP, EPI_SWIGLU>(a, st);
+  return launch_t<SRC_PREP, EPI_STORE>(a, st);
+}
+
+}  // namespace osp

@@ -116,6 +116,8 @@ struct GemvArgs {
   long ld_logits;           // stride between rows of y for logits
   float* part;              // [rows][nblk][4]: max, sumexp, argmax, unused
   int nblk;
+  uint16_t* act_hi;         // SWIGLU of large passes: where silu(g) u goes as pairs [max_rows][N],
+  uint16_t* act_lo;         // when its K is not split (nullable)
   float* split_buf;         // matrix-core K-split partials [split][max_rows][N] (SwiGLU: 2 N)
   // SRC_PREP inputs (bf16 hi / lo pairs)
   const uint16_t* xs_hi;
@@ -161,6 +163,12 @@ void launch_gemv_qkv_pick(const GemvArgs& a, hipStream_t st);
 // SRC_PREP; epi EPI_STORE or EPI_SWIGLU (K-split partial sums into split_buf, summed
 // by the row kernels below) or EPI_LOGITS.  Returns the number of K splits written.
 int launch_gemm(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st);
+// The same for large passes (more than 128 rows) of the shapes it supports (EPI_STORE,
+// EPI_SWIGLU): large tiles, K split only where the tiles leave the chip idle.  Returns the
+// K splits written to split_buf, or 0 when silu(g) u went to act_hi / act_lo instead.
+// input_rows: bound on the row indices read.
+bool gemm_rows_supported(SrcKind src, const GemvArgs& a, long input_rows);
+int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st);
 // True when a pass of `rows` rows takes the matrix-core path.
 bool gemm_use_mfma(int wdtype, int rows);
 int gemm_rows_per_block(EpiKind epi);

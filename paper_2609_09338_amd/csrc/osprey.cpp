@@ -583,6 +583,11 @@ struct TreePass {
   const int32_t* bslot;     // [B] each sequence's cache slot (its committed context)
 };
 
+// A product of a pass of more than kLmMaxRows rows.
+int gemm_large(SrcKind src, EpiKind epi, const GemvArgs& g, long input_rows, hipStream_t st) {
+  return gemm_rows_supported(src, g, input_rows) ? launch_gemm_rows(src, epi, g, st) : launch_gemm(src, epi, g, st);
+}
+
 void run_body_mr(osprey_handle* h, const RowMeta& rows, const int32_t* cu, int B, const float* s_src,
                  int ks_taps, const SplitPlan& sp, int rows_per_seq, int slot0,
                  const TreePass* tree = nullptr, const PickArgs* pick = nullptr) {
@@ -594,7 +599,7 @@ void run_body_mr(osprey_handle* h, const RowMeta& rows, const int32_t* cu, int B
   float* part = skinny ? W.split_s : W.split;
   auto gemm = [&](SrcKind src, EpiKind epi, GemvArgs& g) -> int {
     g.split_buf = part;
-    return skinny ? launch_skinny(src, g, h->stream) : launch_gemm(src, epi, g, h->stream);
+    return skinny ? launch_skinny(src, g, h->stream) : gemm_large(src, epi, g, rows.max_rows, h->stream);
   };
   const int d = c.d_model, hd = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads, F = c.d_ffn;
   const int qkv_w = h->D.qkv_rows;
@@ -744,10 +749,13 @@ void run_body_mr(osprey_handle* h, const RowMeta& rows, const int32_t* cu, int B
     gu.w0 = L.w_gate;
     gu.w1 = L.w_up;
     gu.N = F;
+    // (the vector body's fp32 FFN rows hold the pairs that large passes write themselves)
+    gu.act_hi = reinterpret_cast<uint16_t*>(W.h);
+    gu.act_lo = gu.act_hi + (long)h->D.Rmax * F;
     RowArgs rs = ra;
     rs.W = F;
     rs.ldp = 2 * F;
-    rs.ks = gemm(SRC_PREP, EPI_SWIGLU, gu);
+    rs.ks = gemm(SRC_PREP, EPI_SWIGLU, gu);   // 0: silu(g) u is in gu.act_hi / act_lo
     // down projection; residual + the next layer's input norm (final norm after the last).
     // Passes of up to 16 rows form silu(gate) * up while staging the down projection's
     // inputs (each block re-reads the gate/up partials of its K range, which only stays
@@ -769,7 +777,12 @@ void run_body_mr(osprey_handle* h, const RowMeta& rows, const int32_t* cu, int B
       rd.part = W.split_s2;
       rd.ks = launch_skinny(SRC_SWIGLU, gd, h->stream);
     } else {
-      launch_rows_swiglu(rs, h->stream);
+      if (rs.ks > 0) {
+        launch_rows_swiglu(rs, h->stream);
+      } else {
+        gd.xa_hi = gu.act_hi;
+        gd.xa_lo = gu.act_lo;
+      }
       rd.ks = gemm(SRC_PREP, EPI_STORE, gd);
       rd.part = part;
     }
@@ -1274,7 +1287,9 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
       gt.split_buf = W.split_s;
       ks_taps = launch_skinny(SRC_TAPS, gt, h->stream);
     } else {
-      ks_taps = launch_gemm(SRC_TAPS, EPI_STORE, gt, h->stream);
+      // (tap rows: b taps_stride + j, or packed)
+      const long tap_rows = a->taps_stride > 0 ? (long)B * a->taps_stride : rows;
+      ks_taps = gemm_large(SRC_TAPS, EPI_STORE, gt, tap_rows, h->stream);
     }
     run_body_mr(h, ing, W.cu, B, nullptr, ks_taps, split, max_new + (block_mask >= 0 ? extra : 0), a->slots[0]);
   } else {

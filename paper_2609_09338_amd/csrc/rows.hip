@@ -12,6 +12,8 @@
 #include "internal.h"
 #include "pick.h"
 
+#include <type_traits>
+
 namespace osp {
 
 constexpr int kRowThreads = 256;
@@ -25,22 +27,23 @@ OSP_DEV void store_pair4(uint16_t* hi, uint16_t* lo, long o, float4 v) {
 }
 
 // Sum over the K splits of columns [col, col + 4) of row r, in split order.  The loads
-// of a round of kMaxKSplit splits are requested at once, from clamped addresses: a
-// round's loads past the last split read that split again (a cache hit) and add zero,
-// so no load waits on a condition.  One round covers the projections (at most
-// kMaxKSplit splits); the tap projection over n_taps x target_hidden columns can take
-// more (24 at 3 x 8192), hence the further rounds.
-template <int N>
+// of a round of Q splits are requested at once, from clamped addresses: a round's loads
+// past the last split read that split again (a cache hit) and add zero, so no load waits
+// on a condition.  Q is the power of two that covers the product's splits (rows_launch:
+// large passes split K little or not at all, and 16 loads of one split cost a
+// 1999-row pass 18 instead of 9 us), at most kMaxKSplit; the tap projection over
+// n_taps x target_hidden columns can take more (24 at 3 x 8192), hence the further rounds.
+template <int N, int Q>
 OSP_DEV void add_round4(const float* const (&p)[N], long stride, int k0, int ks, float4 (&s)[N]) {
-  float4 v[N][kMaxKSplit];
+  float4 v[N][Q];
 #pragma unroll
-  for (int q = 0; q < kMaxKSplit; ++q)
+  for (int q = 0; q < Q; ++q)
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j][q] = *reinterpret_cast<const float4*>(p[j] + min(k0 + q, ks - 1) * stride);
 #pragma unroll
   for (int j = 0; j < N; ++j)
 #pragma unroll
-    for (int q = 0; q < kMaxKSplit; ++q) {
+    for (int q = 0; q < Q; ++q) {
       const bool in = k0 + q < ks;
       s[j].x += in ? v[j][q].x : 0.f; s[j].y += in ? v[j][q].y : 0.f;
       s[j].z += in ? v[j][q].z : 0.f; s[j].w += in ? v[j][q].w : 0.f;
@@ -48,7 +51,7 @@ OSP_DEV void add_round4(const float* const (&p)[N], long stride, int k0, int ks,
 }
 
 // Columns [col[j], col[j] + 4) of row r for each j < N (all requested together).
-template <int N>
+template <int N, int Q>
 OSP_DEV void sum_parts(const RowArgs& a, int r, const int (&col)[N], float4 (&s)[N]) {
   const float* p[N];
 #pragma unroll
@@ -58,13 +61,15 @@ OSP_DEV void sum_parts(const RowArgs& a, int r, const int (&col)[N], float4 (&s)
   }
   const long stride = (long)a.max_rows * a.ldp;
   __builtin_assume(a.ks >= 1);   // (every producer writes at least one split)
-  add_round4<N>(p, stride, 0, a.ks, s);
-  for (int k0 = kMaxKSplit; k0 < a.ks; k0 += kMaxKSplit) add_round4<N>(p, stride, k0, a.ks, s);
+  add_round4<N, Q>(p, stride, 0, a.ks, s);
+  if constexpr (Q == kMaxKSplit)
+    for (int k0 = Q; k0 < a.ks; k0 += Q) add_round4<N, Q>(p, stride, k0, a.ks, s);
 }
 
+template <int Q>
 OSP_DEV float4 sum_parts4(const RowArgs& a, int r, int col) {
   float4 s[1];
-  sum_parts<1>(a, r, {col}, s);
+  sum_parts<1, Q>(a, r, {col}, s);
   return s[0];
 }
 
@@ -112,7 +117,7 @@ OSP_DEV void load_gain(const RowArgs& a, uint2 (&gr)[kRowGroups]) {
 // DRAW: row r's token is drawn here from the LM head's records and logits (a.pick), and
 // the conditioning rows s_src may be the rows x that this block overwrites (each thread
 // reads its columns of row r before it writes them).
-template <bool DRAW>
+template <bool DRAW, int Q>
 __global__ void __launch_bounds__(kRowThreads) k_rows_prep(RowArgs a) {
   __shared__ float sm[kRowThreads / 64];
   const int r = blockIdx.x;
@@ -160,7 +165,7 @@ __global__ void __launch_bounds__(kRowThreads) k_rows_prep(RowArgs a) {
     if (c < a.W) {
       float4 v;
       if constexpr (DRAW) v = sv[i];
-      else v = a.s_src ? *reinterpret_cast<const float4*>(a.s_src + (long)r * a.W + c) : sum_parts4(a, r, c);
+      else v = a.s_src ? *reinterpret_cast<const float4*>(a.s_src + (long)r * a.W + c) : sum_parts4<Q>(a, r, c);
       store_pair4(a.s_hi, a.s_lo, (long)r * a.W + c, v);
     }
   }
@@ -190,6 +195,7 @@ __global__ void __launch_bounds__(kRowThreads) k_rows_prep(RowArgs a) {
   }
 }
 
+template <int Q>
 __global__ void __launch_bounds__(kRowThreads) k_rows_resid_norm(RowArgs a) {
   __shared__ float sm[kRowThreads / 64];
   const int r = blockIdx.x;
@@ -209,7 +215,7 @@ __global__ void __launch_bounds__(kRowThreads) k_rows_resid_norm(RowArgs a) {
   for (int i = 0; i < kRowGroups; ++i) {
     const int c = (threadIdx.x + i * kRowThreads) * 4;
     if (c < a.W) {
-      const float4 p = sum_parts4(a, r, c);
+      const float4 p = sum_parts4<Q>(a, r, c);
       v[i].x += p.x; v[i].y += p.y; v[i].z += p.z; v[i].w += p.w;
       *reinterpret_cast<float4*>(a.x + (long)r * a.W + c) = v[i];
       ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
@@ -219,13 +225,14 @@ __global__ void __launch_bounds__(kRowThreads) k_rows_resid_norm(RowArgs a) {
 }
 
 // Elementwise: the columns of a row are spread over gridDim.y blocks.
+template <int Q>
 __global__ void __launch_bounds__(kRowThreads) k_rows_swiglu(RowArgs a) {
   const int r = blockIdx.x;
   const int rows = a.count ? min(*a.count, a.max_rows) : a.max_rows;
   if (r >= rows) return;
   for (int c = (blockIdx.y * kRowThreads + threadIdx.x) * 4; c < a.W; c += gridDim.y * kRowThreads * 4) {
     float4 gu[2];
-    sum_parts<2>(a, r, {c, a.W + c}, gu);
+    sum_parts<2, Q>(a, r, {c, a.W + c}, gu);
     const float4 g = gu[0], u = gu[1];
     const float4 h = make_float4(g.x / (1.0f + __expf(-g.x)) * u.x, g.y / (1.0f + __expf(-g.y)) * u.y,
                                  g.z / (1.0f + __expf(-g.z)) * u.z, g.w / (1.0f + __expf(-g.w)) * u.w);
@@ -233,16 +240,36 @@ __global__ void __launch_bounds__(kRowThreads) k_rows_swiglu(RowArgs a) {
   }
 }
 
+// f(std::integral_constant<int, Q>) with the smallest Q of 1, 2, 4, 8, 16 that covers ks
+// splits (16 also stands for more: further rounds).
+template <typename F>
+static void rows_launch(int ks, F f) {
+  if (ks <= 1) f(std::integral_constant<int, 1>());
+  else if (ks <= 2) f(std::integral_constant<int, 2>());
+  else if (ks <= 4) f(std::integral_constant<int, 4>());
+  else if (ks <= 8) f(std::integral_constant<int, 8>());
+  else f(std::integral_constant<int, kMaxKSplit>());
+}
+
 void launch_rows_prep(const RowArgs& a, hipStream_t st) {
-  if (a.pick.part) hipLaunchKernelGGL(k_rows_prep<true>, dim3(a.max_rows), dim3(kRowThreads), 0, st, a);
-  else hipLaunchKernelGGL(k_rows_prep<false>, dim3(a.max_rows), dim3(kRowThreads), 0, st, a);
+  if (a.pick.part) {
+    hipLaunchKernelGGL((k_rows_prep<true, 1>), dim3(a.max_rows), dim3(kRowThreads), 0, st, a);
+    return;
+  }
+  rows_launch(a.s_src ? 1 : a.ks, [&](auto q) {
+    hipLaunchKernelGGL((k_rows_prep<false, decltype(q)::value>), dim3(a.max_rows), dim3(kRowThreads), 0, st, a);
+  });
 }
 void launch_rows_resid_norm(const RowArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_rows_resid_norm, dim3(a.max_rows), dim3(kRowThreads), 0, st, a);
+  rows_launch(a.ks, [&](auto q) {
+    hipLaunchKernelGGL((k_rows_resid_norm<decltype(q)::value>), dim3(a.max_rows), dim3(kRowThreads), 0, st, a);
+  });
 }
 void launch_rows_swiglu(const RowArgs& a, hipStream_t st) {
   const int per_row = (a.W + kRowThreads * 4 - 1) / (kRowThreads * 4);   // one column group per block
-  hipLaunchKernelGGL(k_rows_swiglu, dim3(a.max_rows, per_row), dim3(kRowThreads), 0, st, a);
+  rows_launch(a.ks, [&](auto q) {
+    hipLaunchKernelGGL((k_rows_swiglu<decltype(q)::value>), dim3(a.max_rows, per_row), dim3(kRowThreads), 0, st, a);
+  });
 }
 
 }  // namespace osp
