@@ -26,7 +26,7 @@
 // a pass of too few tiles to fill the chip splits its context, and the merge kernel or
 // the O projection joins the partials.
 // Measured per layer: one 1999-token prompt (16 / 8 heads x 128) 1422 -> 78 us; four of 8200
-// tokens in all (32 / 8 heads x 128) 5600 -> 586 us; two turns of 770 tokens over 6000-8000
+// tokens in all (32 / 8 heads x 128) 5850 -> 586 us; two turns of 770 tokens over 6000-8000
 // cached positions (16 / 8 x 128) 672 -> 216 us; a 17-row block (32 / 8 x 64) 24.2 -> 12.3 us.
 #include "common.h"
 #include "internal.h"
@@ -282,6 +282,57 @@ __global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles) {
       }
     }
   }
+}
+
+// Merge of a few splits for many rows: a wavefront per (row, head), lane l holding
+// HD / 64 dimensions of every split, the splits' loads four at a time.  (The general
+// merge kernel gives each (row, head) a block with slots for 64 splits: 81 us for two
+// splits of 1999 x 16 rows.)
+template <int HD>
+__global__ void __launch_bounds__(256) k_attn_join(AttnArgs a) {
+  constexpr int DPL = HD / 64;
+  const int r = blockIdx.x, h = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int rows = a.rows.count ? min(*a.rows.count, a.rows.max_rows) : a.rows.max_rows;
+  if (r >= rows || h >= a.nq) return;
+  const float* pp = a.part + ((long)r * a.nq + h) * a.n_split * (HD + 2);
+  // splits that hold a position this row sees (later ones were not written)
+  const int ns = min(a.n_split, a.rows.pos[r] / a.split_len + 1);
+  const long rec = (long)min(lane, ns - 1) * (HD + 2);
+  const float2 ml = *reinterpret_cast<const float2*>(pp + rec);
+  const float m = lane < ns ? ml.x : -INFINITY;
+  const float M = wave_max(m);
+  const float f = m > -INFINITY ? __expf(m - M) : 0.f;
+  const float L = wave_sum(lane < ns ? ml.y * f : 0.f);
+  const float w = L > 0.f ? f / L : 0.f;
+  float y[DPL];
+#pragma unroll
+  for (int e = 0; e < DPL; ++e) y[e] = 0.f;
+  for (int s0 = 0; s0 < ns; s0 += 4) {
+    float v[4][DPL];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < DPL; ++e) v[i][e] = pp[(long)min(s0 + i, ns - 1) * (HD + 2) + 2 + lane * DPL + e];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float ws = s0 + i < ns ? lane_f(w, min(s0 + i, 63)) : 0.f;
+#pragma unroll
+      for (int e = 0; e < DPL; ++e) y[e] += s0 + i < ns ? v[i][e] * ws : 0.f;
+    }
+  }
+  const long o = (long)r * a.nq * HD + h * HD + lane * DPL;
+#pragma unroll
+  for (int e = 0; e < DPL; ++e) {
+    const bf16_t yh = f32_to_bf16(y[e]);
+    a.o_hi[o + e] = yh;
+    a.o_lo[o + e] = f32_to_bf16(y[e] - bf16_to_f32(yh));
+  }
+}
+
+void launch_attn_join(const AttnArgs& a, hipStream_t st) {
+  const dim3 grid(a.rows.max_rows, (a.nq + 3) / 4);
+  if (a.hd == 128) hipLaunchKernelGGL(k_attn_join<128>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(k_attn_join<64>, grid, dim3(256), 0, st, a);
 }
 
 // Two query tiles per wavefront once a sequence fills more than one block of them.

@@ -310,6 +310,8 @@ void launch_attention(int kvdtype, const AttnArgs& a, hipStream_t st);
 bool attn_rows_supported(int kvdtype, int rows_per_seq, int group);
 int attn_rows_tiles(int rows_per_seq, int group);
 void launch_attention_rows(const AttnArgs& a, hipStream_t st);
+// The merge of its splits into o_hi / o_lo (not for tree passes).
+void launch_attn_join(const AttnArgs& a, hipStream_t st);
 // Matrix-core path: per row, sum the QKV split partials, normalise and rotate q
 // and k, write q * (1/sqrt(hd)) to q_out and the new k, v into the cache.
 void launch_rows_qkv(int kvdtype, const AttnArgs& a, float* q_out, hipStream_t st);
