@@ -697,7 +697,9 @@ __global__ void __launch_bounds__(256) k_rows_qkv(AttnArgs a, float* q_out) {
   const int rows = a.rows.count ? min(*a.rows.count, a.rows.max_rows) : a.rows.max_rows;
   if (r >= rows) return;
   const int lane = threadIdx.x & 63;
-  const int hh = blockIdx.y * 4 + (threadIdx.x >> 6);
+  // (kv_only: rows hold keys and values alone)
+  const int h0 = a.kv_only ? a.nq : 0;
+  const int hh = h0 + blockIdx.y * 4 + (threadIdx.x >> 6);
   if (hh >= a.nq + a.nkv) return;
   // (a draft-tree row: its own position for RoPE; rows.pos bounds the context read)
   const int pos = a.tree_pos ? a.tree_pos[r] : a.rows.pos[r];
@@ -715,8 +717,8 @@ __global__ void __launch_bounds__(256) k_rows_qkv(AttnArgs a, float* q_out) {
     return;
   }
   const int g = hh - a.nq;
-  const long ko = (long)r * a.qkv_w + (long)(a.nq + g) * HD;
-  const long vo = (long)r * a.qkv_w + (long)(a.nq + a.nkv + g) * HD;
+  const long ko = (long)r * a.qkv_w + (long)(a.nq - h0 + g) * HD;
+  const long vo = ko + (long)a.nkv * HD;
   float kv[4];
   qkv_lanes<HD, true, 2, true>(a, {ko, vo}, lane, kv);
   float k1 = kv[0], k2 = kv[1];
@@ -909,7 +911,7 @@ void launch_attention(int kvdtype, const AttnArgs& a, hipStream_t st) {
 }
 
 void launch_rows_qkv(int kvdtype, const AttnArgs& a, float* q_out, hipStream_t st) {
-  dim3 grid(a.rows.max_rows, (a.nq + a.nkv + 3) / 4);
+  dim3 grid(a.rows.max_rows, ((a.kv_only ? 0 : a.nq) + a.nkv + 3) / 4);
   if (kvdtype == 1) {
     if (a.hd == 128) hipLaunchKernelGGL((k_rows_qkv<bf16_t, 128>), grid, dim3(256), 0, st, a, q_out);
     else hipLaunchKernelGGL((k_rows_qkv<bf16_t, 64>), grid, dim3(256), 0, st, a, q_out);

@@ -239,6 +239,19 @@ void launch_rows_prep(const RowArgs& a, hipStream_t st);
 void launch_rows_resid_norm(const RowArgs& a, hipStream_t st);
 // out = silu(sum of gate partials) * sum of up partials (columns [0, W) and [W, 2 W)).
 void launch_rows_swiglu(const RowArgs& a, hipStream_t st);
+// Narrows a pass to n of its rows, in place: row b of every array becomes row gather[b]
+// (ascending, gather[b] >= b); pos[b] = committed[b] - 1.
+struct KeepArgs {
+  int n;
+  const int32_t* gather;
+  const int32_t* committed;
+  int32_t* pos;
+  struct {
+    void* p;                // 16-byte aligned rows
+    int pieces;             // 16-byte pieces per row
+  } a[5];                   // (unused: null)
+};
+void launch_rows_keep(const KeepArgs& a, hipStream_t st);
 // Partition of the N weight rows of a launch: each wavefront owns rows_per_wave
 // consecutive rows; `waves` wavefronts carry rows (the logits epilogue writes
 // one statistics record per wavefront).
@@ -257,6 +270,7 @@ struct AttnArgs {
   int slot0;                // the slot of sequence 0 when B == 1 (no load); -1: bslot
   int B;
   int rows_per_seq;         // host bound on the rows of one sequence in this pass
+  int kv_only;              // launch_rows_qkv: qkv holds keys and values only; they are appended
   const float* qkv;         // [rows][qkv_w] raw projections (split 0 of qkv_ks partials)
   int qkv_w;
   int qkv_ks;               // K-split partials to sum on load (1: plain rows)
@@ -488,7 +502,7 @@ struct TreeArgs {
   float* r_s;               // [rows][d] conditioning input: the parent's hidden state
   const float* x;           // this pass's body output rows (root pass: the ingest rows)
   int d;
-  const int32_t* last_row;
+  const int32_t* last_row;  // the root's rows of x (nullable: row b)
   const int32_t* committed;
   int32_t* out_tok;         // [B][n_nodes]
   int32_t* out_par;

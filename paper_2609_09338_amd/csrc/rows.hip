@@ -240,6 +240,33 @@ __global__ void __launch_bounds__(kRowThreads) k_rows_swiglu(RowArgs a) {
   }
 }
 
+// A thread owns one 16-byte column of one array and moves it row by row, so that no other
+// thread's write can meet its reads; the rows of a round are read before any is written
+// (row b's source is row b or later, and later rounds' sources lie past this round's rows).
+__global__ void __launch_bounds__(kRowThreads) k_rows_keep(KeepArgs a) {
+  constexpr int R = 16;
+  const int y = blockIdx.y, i = blockIdx.x * kRowThreads + threadIdx.x;
+  if (y == 0 && i < a.n) a.pos[i] = a.committed[i] - 1;
+  if (i >= a.a[y].pieces) return;
+  uint4* p = reinterpret_cast<uint4*>(a.a[y].p) + i;
+  const long ld = a.a[y].pieces;
+  for (int b0 = 0; b0 < a.n; b0 += R) {
+    uint4 v[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[q] = p[a.gather[min(b0 + q, a.n - 1)] * ld];
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (b0 + q < a.n) p[(b0 + q) * ld] = v[q];
+  }
+}
+
+void launch_rows_keep(const KeepArgs& a, hipStream_t st) {
+  int arrays = 0, pieces = a.n;
+  for (const auto& x : a.a)
+    if (x.p) { ++arrays; pieces = pieces > x.pieces ? pieces : x.pieces; }
+  hipLaunchKernelGGL(k_rows_keep, dim3((pieces + kRowThreads - 1) / kRowThreads, arrays), dim3(kRowThreads), 0, st, a);
+}
+
 // f(std::integral_constant<int, Q>) with the smallest Q of 1, 2, 4, 8, 16 that covers ks
 // splits (16 also stands for more: further rounds).
 template <typename F>

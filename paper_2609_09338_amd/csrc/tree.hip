@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
 #pragma unroll 4
   for (int i = tid; i < nv; i += kTkThreads) {
     const int j = i / d4;
-    const int src = p == 0 ? a.last_row[b] : b * K + s_src[j];
+    const int src = p == 0 ? (a.last_row ? a.last_row[b] : b) : b * K + s_src[j];
     s4[i] = x4[(long)src * d4 + (i - j * d4)];
   }
 }
