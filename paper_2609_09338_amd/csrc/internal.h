@@ -468,19 +468,15 @@ void launch_verify_tree(const VerifyArgs& a, hipStream_t st);
 constexpr int kMaxTopk = 8;           // children per node
 constexpr int kMaxTreeDepth = 8;      // depths
 constexpr int kMaxTreeProc = 64;      // frontier nodes run through the drafter per sequence
-constexpr int kTkRecordRows = 64;    // tree passes of at least this many rows select from the records
 constexpr int kTkMaxRecords = 2048;   // LM-head records per row a draft tree takes (V_d <= 2048 x 128)
 constexpr int kMaxCand = 512;         // candidates per sequence (>= 8 + 7 x 64)
-constexpr int kTkBlocks = 64;         // blocks per LM-head row in the candidate pass
+constexpr int kTkMaxVocab = 262144;   // LM-head rows a draft tree takes
 struct TreeArgs {
   int B, k, depth, pass, n_nodes;
   int V;                    // LM-head rows
   const int32_t* d2t;
   const float* logits;      // rows of this pass at logits + r * ld_logits
   long ld_logits;
-  float* cand_v;            // [rows][kTkBlocks][kMaxTopk] best (logit, row) pairs per block
-                            // (nullptr: the step kernel selects from the records)
-  int32_t* cand_r;
   const float* rec;         // LM-head records [rows][nblk][4] at temperature 1
   int nblk;
   int blk_rows;              // logits per record
@@ -508,7 +504,6 @@ struct TreeArgs {
   int32_t* out_par;
   double* out_score;        // [B][n_nodes] (nullable)
 };
-void launch_tree_topk(const TreeArgs& a, int rows, hipStream_t st);
 void launch_tree_step(const TreeArgs& a, hipStream_t st);
 void launch_tree_final(const TreeArgs& a, hipStream_t st);
 

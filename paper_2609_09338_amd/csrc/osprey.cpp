@@ -92,8 +92,6 @@ struct Ws {
   int32_t* tree_removed;
   // draft-tree growth
   void* tree_kv;              // [B * kMaxTreeProc][n_layers][2][nkv][hd], cache dtype
-  float* tree_cv;             // [B * kMaxTopk][kTkBlocks][kMaxTopk]
-  int32_t* tree_cr;
   int32_t *c_tok, *c_par, *c_depth, *c_slot, *n_cand, *front;   // [B][kMaxCand] / [B] / [B][kMaxTopk]
   double* c_score;
   int32_t *r_tok, *r_pos, *r_attpos, *r_node, *r_anc;  // [B * kMaxTopk] (r_anc x kMaxTreeDepth)
@@ -199,8 +197,6 @@ size_t plan(const osprey_config& c, char* base, Ws* w) {
     const long el = c.dtype == OSPREY_BF16 ? 2 : 4;
     const long rows = (long)D.B * kMaxTopk;
     W.tree_kv = take(el * D.B * kMaxTreeProc * c.n_layers * 2 * c.n_kv_heads * c.head_dim);
-    W.tree_cv = (float*)take(4L * rows * kTkBlocks * kMaxTopk);
-    W.tree_cr = (int32_t*)take(4L * rows * kTkBlocks * kMaxTopk);
     W.c_tok = (int32_t*)take(4L * D.B * kMaxCand);
     W.c_par = (int32_t*)take(4L * D.B * kMaxCand);
     W.c_depth = (int32_t*)take(4L * D.B * kMaxCand);
@@ -797,10 +793,10 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
     a.n_split = sp.n_split;
     a.split_len = sp.split_len;
     a.kv_stream = sp.kv_stream;
-    // the longest-first work list only matters for several sequences (it lists the
-    // step's sequences, not a tree pass's branches)
-    a.items = (B == 1 || tree) ? nullptr : W.attn_items;
-    a.n_items = (B == 1 || tree) ? nullptr : W.attn_n_items;
+    // the longest-first work list only matters for several sequences (a tree pass's rows
+    // attend to the committed contexts it lists)
+    a.items = B == 1 ? nullptr : W.attn_items;
+    a.n_items = B == 1 ? nullptr : W.attn_n_items;
     if (tree) {
       a.tree_node = tree->node;
       a.tree_anc = tree->anc;
@@ -1563,7 +1559,7 @@ OSPREY_API int osprey_draft_tree(osprey_handle* h, const osprey_step_args* a, co
   if (N < 1 || N > std::min(kMaxTreeNodes, n_cand))
     return fail(OSPREY_E_INVALID, "n_nodes %d not in [1, %d]", N, std::min(kMaxTreeNodes, n_cand));
   if (!t->tokens || !t->parents) return fail(OSPREY_E_INVALID, "tree outputs are NULL");
-  if (c.vocab_draft > kTkBlocks * 256 * 16 ||
+  if (c.vocab_draft > kTkMaxVocab ||
       lm_head_plan(std::min(B * k, kLmMaxRows), c.vocab_draft, h->n_cu).nblk > kTkMaxRecords)
     return fail(OSPREY_E_UNSUPPORTED, "vocab_draft %d too large for trees", c.vocab_draft);
   SplitPlan split;
@@ -1581,8 +1577,6 @@ OSPREY_API int osprey_draft_tree(osprey_handle* h, const osprey_step_args* a, co
   ta.d2t = h->w.d2t;
   ta.logits = W.logits;
   ta.ld_logits = c.vocab_draft;
-  ta.cand_v = W.tree_cv;
-  ta.cand_r = W.tree_cr;
   ta.rec = W.lm_part;
   ta.c_tok = W.c_tok;
   ta.c_par = W.c_par;
@@ -1608,16 +1602,11 @@ OSPREY_API int osprey_draft_tree(osprey_handle* h, const osprey_step_args* a, co
   ta.out_score = t->scores;
   // the root: the last ingest row of every sequence
   ta.pass = 0;
-  // passes of many rows select their top-k from the LM-head records in the step kernel;
-  // few rows spread each row over kTkBlocks blocks of a separate pass first
-  auto select = [&](int rows, const LmPlan& lp) {
+  auto select = [&](const LmPlan& lp) {
     ta.nblk = lp.nblk;
     ta.blk_rows = lp.blk_rows;
-    ta.cand_v = rows >= kTkRecordRows ? nullptr : W.tree_cv;
-    ta.cand_r = W.tree_cr;
-    if (ta.cand_v) launch_tree_topk(ta, rows, h->stream);
   };
-  select(B, run_head_tree(h, B, root_rows, rc));
+  select(run_head_tree(h, B, root_rows, rc));
   if (rc) return rc;
   launch_tree_step(ta, h->stream);
   // every further depth: the frontier's B k rows through the body and the LM head
@@ -1627,7 +1616,7 @@ OSPREY_API int osprey_draft_tree(osprey_handle* h, const osprey_step_args* a, co
     TreePass tp{W.r_node, W.r_anc, W.r_pos, W.bslot};
     run_body_mr(h, rm, W.r_cu, B, W.r_s, 1, split, k, -1, &tp);
     ta.pass = p;
-    select(rows, run_head_tree(h, rows, nullptr, rc));
+    select(run_head_tree(h, rows, nullptr, rc));
     if (rc) return rc;
     launch_tree_step(ta, h->stream);
   }

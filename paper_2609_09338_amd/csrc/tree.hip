@@ -4,15 +4,21 @@
 // the k best candidates of a depth form the next frontier, and the n best candidates
 // of all depths form the tree.
 //
-//   k_tree_topk  (rows x 64)  the k best (logit, row) pairs of each 1/64 of an LM-head
-//                             row (larger logit first, lower row on ties)
-//   k_tree_step  (B)          per sequence: the rows' k best pairs and log-normalisers
-//                             (LM-head records at temperature 1), the new candidates,
-//                             the next frontier and the next pass's rows: token, position,
-//                             node slot, ancestors' slots and conditioning row (the
-//                             parent's hidden state)
-//   k_tree_final (B)          the n best candidates in generation order, parents
-//                             re-indexed
+//   k_tree_step  (B)  per sequence: the rows' k best (logit, row) pairs (larger logit
+//                     first, lower row on ties) and log-normalisers, both from the LM-head
+//                     records at temperature 1, the new candidates, the next frontier and
+//                     the next pass's rows: token, position, node slot, ancestors' slots
+//                     and conditioning row (the parent's hidden state)
+//   k_tree_final (B)  the n best candidates in generation order, parents re-indexed
+//
+// A wavefront selects a row's k best: the k-th largest of the distinct range maxima in the
+// records bounds them from below (at least k values reach it), so only the logits of the
+// ranges that reach it are read, and those that reach it themselves, hardly more than k,
+// are ranked against each other in one step.  Latency-bound: two dependent loads (records,
+// logits) and about 1 us of arithmetic.  (Rounds of a wavefront arg-best over the 32
+// records and 32 logits of every lane, two rows per wavefront, took 65 us per step for 12
+// sequences of 8 rows, now 20; for one sequence of 4 rows a separate pass over every logit
+// took 7.5 us before a step of 13.4, now one step of 14.6.)
 // A frontier row's attention over its ancestors' and its own keys/values (the tree
 // cache) is one more split of the context attention, added by the split combine.
 #include "common.h"
@@ -20,8 +26,7 @@
 
 namespace osp {
 
-constexpr int kTkThreads = 256;
-constexpr int kTkPer = 16;        // logits per thread and block: a row of up to 64 x 4096
+constexpr int kTkThreads = kMaxTopk * OSP_WAVE;   // a wavefront per frontier row
 constexpr int kTkRecLane = kTkMaxRecords / OSP_WAVE;   // LM-head records per lane
 
 OSP_DEV bool tk_better(float v1, int r1, float v2, int r2) { return v1 > v2 || (v1 == v2 && r1 < r2); }
@@ -36,59 +41,11 @@ OSP_DEV void wave_best(float& v, int& r) {
   }
 }
 
-__global__ void __launch_bounds__(kTkThreads) k_tree_topk(TreeArgs a) {
-  __shared__ float s_v[kTkThreads / OSP_WAVE][kMaxTopk];
-  __shared__ int s_r[kTkThreads / OSP_WAVE][kMaxTopk];
-  const int row = blockIdx.x, blk = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int K = a.k;
-  const int chunk = (a.V + kTkBlocks - 1) / kTkBlocks;
-  const int i0 = blk * chunk, i1 = min(a.V, i0 + chunk);
-  const float* lg = a.logits + (long)row * a.ld_logits;
-  float v[kTkPer];
-  int idx[kTkPer];
-#pragma unroll
-  for (int q = 0; q < kTkPer; ++q) {
-    const int i = i0 + tid + q * kTkThreads;
-    const float l = lg[min(i, a.V - 1)];          // clamped address, masked below
-    v[q] = i < i1 ? l : -INFINITY;
-    idx[q] = i < i1 ? i : 0x7fffffff;
-  }
-  // the wavefront's K best: K rounds of a wavefront arg-best, the winner removed
-  for (int t = 0; t < K; ++t) {
-    float bv = -INFINITY;
-    int br = 0x7fffffff;
-#pragma unroll
-    for (int q = 0; q < kTkPer; ++q)
-      if (tk_better(v[q], idx[q], bv, br)) { bv = v[q]; br = idx[q]; }
-    float wv = bv;
-    int wr = br;
-    wave_best(wv, wr);
-#pragma unroll
-    for (int q = 0; q < kTkPer; ++q)
-      if (idx[q] == wr && wr != 0x7fffffff) { v[q] = -INFINITY; idx[q] = 0x7fffffff; }
-    if (lane == 0) { s_v[wave][t] = wv; s_r[wave][t] = wr; }
-  }
-  __syncthreads();
-  if (wave == 0) {
-    const int nc = (kTkThreads / OSP_WAVE) * K;
-    float cv = lane < nc ? s_v[lane / K][lane % K] : -INFINITY;
-    int cr = lane < nc ? s_r[lane / K][lane % K] : 0x7fffffff;
-    const long o = ((long)row * kTkBlocks + blk) * kMaxTopk;
-    for (int t = 0; t < K; ++t) {
-      float wv = cv;
-      int wr = cr;
-      wave_best(wv, wr);
-      if (cr == wr && wr != 0x7fffffff) { cv = -INFINITY; cr = 0x7fffffff; }
-      if (lane == 0) { a.cand_v[o + t] = wv; a.cand_r[o + t] = wr; }
-    }
-  }
-}
-
 // Candidate c is better than candidate e: larger score, lower index on ties.
 OSP_DEV bool cand_better(double s1, int i1, double s2, int i2) { return s1 > s2 || (s1 == s2 && i1 < i2); }
 
-constexpr int kTkRanges = 16;     // record ranges a record-guided selection reads (else the row)
+constexpr int kTkRanges = 16;     // record ranges a selection reads (else the row)
+constexpr int kTkList = OSP_WAVE; // logits it ranks (else the row)
 
 // This lane's kMaxTopk best (value, index) pairs, best first: insert one.
 OSP_DEV void top_insert(float (&bv)[kMaxTopk], int (&br)[kMaxTopk], float v, int r) {
@@ -119,29 +76,6 @@ OSP_DEV void wave_pop_best(float (&bv)[kMaxTopk], int (&br)[kMaxTopk], float& wv
   }
 }
 
-// K rounds of the wavefront's best (value, index) pair over the lanes' N pairs, each
-// winner dropped by its lane; lane 0 writes the winners to ov / orr when given.  Returns
-// the K-th winner's value.
-template <int N>
-OSP_DEV float wave_topk(const float (&v)[N], const int (&ix)[N], int K, float* ov, int* orr) {
-  unsigned long long gone = 0ull;
-  float last = -INFINITY;
-  for (int t = 0; t < K; ++t) {
-    float bv = -INFINITY;
-    int br = 0x7fffffff, bq = -1;
-#pragma unroll
-    for (int q = 0; q < N; ++q)
-      if (!((gone >> q) & 1ull) && tk_better(v[q], ix[q], bv, br)) { bv = v[q]; br = ix[q]; bq = q; }
-    float wv = bv;
-    int wr = br;
-    wave_best(wv, wr);
-    if (bq >= 0 && br == wr && wr != 0x7fffffff) gone |= 1ull << bq;
-    if (ov && (threadIdx.x & 63) == 0) { ov[t] = wv; orr[t] = wr; }
-    last = wv;
-  }
-  return last;
-}
-
 __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
   __shared__ float s_cv[kMaxTopk][kMaxTopk];
   __shared__ int s_cr[kMaxTopk][kMaxTopk];
@@ -153,6 +87,8 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
   __shared__ int s_ntok[kMaxTopk * kMaxTopk], s_ndep[kMaxTopk * kMaxTopk];
   __shared__ int s_rank[kMaxTopk * kMaxTopk];
   __shared__ int s_rng[kMaxTopk][kTkRanges];
+  __shared__ float s_lv[kMaxTopk][kTkList];
+  __shared__ int s_li[kMaxTopk][kTkList];
   __shared__ int s_n0;
   const int b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -168,8 +104,8 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
   if (tid == 0) s_n0 = p == 0 ? 0 : a.n_cand[b];   // (read before anyone writes it below)
   if (tid < K) { s_sel[tid] = tid; s_src[tid] = p == 0 ? 0 : tid; }   // (overwritten below)
   // ---- each row's K best (logit, row) pairs and its log-normaliser M + log S --------------
-  for (int j = wave; j < nfr; j += kTkThreads / OSP_WAVE) {
-    const int r = row0 + j;
+  if (wave < nfr) {
+    const int j = wave, r = row0 + j;
     // LM-head records of the row (temperature 1): max and rescaled sums, every record
     // of the lane requested at once (clamped addresses; lane l: records l, l + 64, ...)
     const float* rec = a.rec + (long)r * a.nblk * 4;
@@ -187,86 +123,72 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
     for (int q = 0; q < kTkRecLane; ++q)
       if (lane + q * OSP_WAVE < a.nblk && rs[q].x > -INFINITY) s += (double)rs[q].y * (double)__expf(rs[q].x - M);
     const double S = wave_sum_d(s);
-    if (!a.cand_v) {
-      // record-guided (passes of many rows): the K best logits lie in ranges whose max
-      // reaches Mk, the K-th largest range max (the K ranges of largest max hold K values
-      // >= Mk, so the K-th best value is >= Mk); only those ranges are read
-      float mv[kTkRecLane];
-      int mi[kTkRecLane];
+    // Mk: the K-th largest distinct range max (the ranges of largest max hold K values >= Mk,
+    // so the K-th best value is >= Mk)
+    float Mk = M;
+    for (int t = 1; t < K; ++t) {
+      float x = -INFINITY;
 #pragma unroll
       for (int q = 0; q < kTkRecLane; ++q) {
-        const bool in = lane + q * OSP_WAVE < a.nblk;
-        mv[q] = in ? rs[q].x : -INFINITY;
-        mi[q] = in ? lane + q * OSP_WAVE : 0x7fffffff;
+        const float v = lane + q * OSP_WAVE < a.nblk ? rs[q].x : -INFINITY;
+        x = fmaxf(x, v < Mk ? v : -INFINITY);
       }
-      const float Mk = wave_topk(mv, mi, K, nullptr, nullptr);
-      int n = 0;
+      Mk = wave_max(x);
+    }
+    int n = 0;
 #pragma unroll
-      for (int q = 0; q < kTkRecLane; ++q) {
-        const int c = lane + q * OSP_WAVE;
-        const bool in = c < a.nblk && rs[q].x >= Mk;
+    for (int q = 0; q < kTkRecLane; ++q) {
+      const int c = lane + q * OSP_WAVE;
+      const bool in = c < a.nblk && rs[q].x >= Mk;
+      const unsigned long long bal = __ballot(in);
+      const int at = n + __popcll(bal & ((1ull << lane) - 1ull));
+      if (in && at < kTkRanges) s_rng[j][at] = c;
+      n += __popcll(bal);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const float* lg = a.logits + (long)r * a.ld_logits;
+    int nl = kTkList + 1;
+    if (n <= kTkRanges && Mk > -INFINITY) {
+      // every listed range's logits requested at once: lane l reads entries l and l + 64
+      float lv[2 * kTkRanges];
+#pragma unroll
+      for (int i = 0; i < kTkRanges; ++i) {
+        const int e0 = (i < n ? s_rng[j][i] : 0) * a.blk_rows + lane;
+        lv[2 * i] = lg[min(e0, a.V - 1)];                  // clamped, masked below
+        lv[2 * i + 1] = lg[min(e0 + OSP_WAVE, a.V - 1)];
+      }
+      // those that reach Mk into a list
+      nl = 0;
+#pragma unroll
+      for (int i = 0; i < 2 * kTkRanges; ++i) {
+        const int at = (i & 1) * OSP_WAVE + lane;            // place in the range
+        const int e = (i / 2 < n ? s_rng[j][i / 2] : 0) * a.blk_rows + at;
+        const bool in = i / 2 < n && at < a.blk_rows && e < a.V && lv[i] >= Mk;
         const unsigned long long bal = __ballot(in);
-        const int at = n + __popcll(bal & ((1ull << lane) - 1ull));
-        if (in && at < kTkRanges) s_rng[j][at] = c;
-        n += __popcll(bal);
+        const int to = nl + __popcll(bal & ((1ull << lane) - 1ull));
+        if (in && to < kTkList) { s_lv[j][to] = lv[i]; s_li[j][to] = e; }
+        nl += __popcll(bal);
       }
       __builtin_amdgcn_wave_barrier();
-      const float* lg = a.logits + (long)r * a.ld_logits;
-      if (n <= kTkRanges) {
-        // every listed range's logits requested at once: lane l reads entries l and l + 64
-        float lv[2 * kTkRanges];
-        int li[2 * kTkRanges];
-#pragma unroll
-        for (int i = 0; i < kTkRanges; ++i) {
-          const int e0 = (i < n ? s_rng[j][i] : 0) * a.blk_rows + lane, e1 = e0 + OSP_WAVE;
-          const float l0 = lg[min(e0, a.V - 1)], l1 = lg[min(e1, a.V - 1)];   // clamped, masked below
-          const bool in0 = i < n && lane < a.blk_rows && e0 < a.V;
-          const bool in1 = i < n && lane + OSP_WAVE < a.blk_rows && e1 < a.V;
-          lv[2 * i] = in0 ? l0 : -INFINITY;
-          li[2 * i] = in0 ? e0 : 0x7fffffff;
-          lv[2 * i + 1] = in1 ? l1 : -INFINITY;
-          li[2 * i + 1] = in1 ? e1 : 0x7fffffff;
-        }
-        wave_topk(lv, li, K, s_cv[j], s_cr[j]);
-      } else {
-        // ties or masked rows put more ranges at Mk: the whole row
-        float bv[kMaxTopk];
-        int br[kMaxTopk];
-#pragma unroll
-        for (int i = 0; i < kMaxTopk; ++i) { bv[i] = -INFINITY; br[i] = 0x7fffffff; }
-        for (int i = lane; i < a.V; i += OSP_WAVE) top_insert(bv, br, lg[i], i);
-        for (int t = 0; t < K; ++t) {
-          float wv;
-          int wr;
-          wave_pop_best(bv, br, wv, wr);
-          if (lane == 0) { s_cv[j][t] = wv; s_cr[j][t] = wr; }
-        }
-      }
+    }
+    if (nl >= K && nl <= kTkList) {
+      // lane l holds entry l; its rank is the number of better ones
+      const float v = s_lv[j][min(lane, nl - 1)];
+      const int e = s_li[j][min(lane, nl - 1)];
+      int rank = lane < nl ? 0 : K;
+      for (int i = 0; i < nl; ++i) rank += tk_better(s_lv[j][i], s_li[j][i], v, e) ? 1 : 0;
+      if (rank < K) { s_cv[j][rank] = v; s_cr[j][rank] = e; }
     } else {
-      // the blocks' candidates: kTkBlocks x K pairs, lane l holds pairs l, l + 64, ...
-      constexpr int NPL = kTkBlocks * kMaxTopk / OSP_WAVE;
-      float cv[NPL];
-      int cr[NPL];
+      // ties or masked rows put more ranges or logits at Mk: the whole row
+      float bv[kMaxTopk];
+      int br[kMaxTopk];
 #pragma unroll
-      for (int q = 0; q < NPL; ++q) {
-        const int e = lane + q * OSP_WAVE;            // pair e = block e / kMaxTopk, rank e % kMaxTopk
-        const bool in = e % kMaxTopk < K;
-        const long o = ((long)r * kTkBlocks) * kMaxTopk + e;
-        cv[q] = in ? a.cand_v[o] : -INFINITY;
-        cr[q] = in ? a.cand_r[o] : 0x7fffffff;
-      }
+      for (int i = 0; i < kMaxTopk; ++i) { bv[i] = -INFINITY; br[i] = 0x7fffffff; }
+      for (int i = lane; i < a.V; i += OSP_WAVE) top_insert(bv, br, lg[i], i);
       for (int t = 0; t < K; ++t) {
-        float bv = -INFINITY;
-        int br = 0x7fffffff;
-#pragma unroll
-        for (int q = 0; q < NPL; ++q)
-          if (tk_better(cv[q], cr[q], bv, br)) { bv = cv[q]; br = cr[q]; }
-        float wv = bv;
-        int wr = br;
-        wave_best(wv, wr);
-#pragma unroll
-        for (int q = 0; q < NPL; ++q)
-          if (cr[q] == wr && wr != 0x7fffffff) { cv[q] = -INFINITY; cr[q] = 0x7fffffff; }
+        float wv;
+        int wr;
+        wave_pop_best(bv, br, wv, wr);
         if (lane == 0) { s_cv[j][t] = wv; s_cr[j][t] = wr; }
       }
     }
@@ -363,46 +285,45 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
   }
 }
 
-__global__ void __launch_bounds__(kTkThreads) k_tree_final(TreeArgs a) {
+// A thread per candidate; the kept candidates' places come from the wavefronts' ballots.
+__global__ void __launch_bounds__(kMaxCand) k_tree_final(TreeArgs a) {
+  constexpr int kWaves = kMaxCand / OSP_WAVE;
   __shared__ double s_sc[kMaxCand];
   __shared__ int s_keep[kMaxCand];
   __shared__ int s_pos[kMaxCand];
-  const int b = blockIdx.x, tid = threadIdx.x;
+  __shared__ unsigned long long s_bal[kWaves];
+  const int b = blockIdx.x, c = threadIdx.x, lane = c & 63, wave = c >> 6;
   const long cb = (long)b * kMaxCand;
   const int n = min(a.n_cand[b], kMaxCand);
   const int N = min(a.n_nodes, n);
-  for (int c = tid; c < n; c += kTkThreads) s_sc[c] = a.c_score[cb + c];
+  const double mine = c < n ? a.c_score[cb + c] : 0.0;
+  s_sc[c] = mine;
   __syncthreads();
-  for (int c = tid; c < n; c += kTkThreads) {
-    int rank = 0;
-    for (int e = 0; e < n; ++e) rank += cand_better(s_sc[e], e, s_sc[c], c) ? 1 : 0;
-    s_keep[c] = rank < N ? 1 : 0;
-  }
+  int rank = 0;
+#pragma unroll 8
+  for (int e = 0; e < n; ++e) rank += cand_better(s_sc[e], e, mine, c) ? 1 : 0;
+  const bool keep = c < n && rank < N;
+  const unsigned long long bal = __ballot(keep);
+  if (lane == 0) s_bal[wave] = bal;
+  s_keep[c] = keep ? 1 : 0;
   __syncthreads();
-  for (int c = tid; c < n; c += kTkThreads) {
-    int pos = 0;
-    for (int e = 0; e < c; ++e) pos += s_keep[e];
-    s_pos[c] = pos;
-  }
+  int pos = __popcll(bal & ((1ull << lane) - 1ull));
+  for (int w = 0; w < wave; ++w) pos += __popcll(s_bal[w]);
+  s_pos[c] = pos;
   __syncthreads();
-  for (int c = tid; c < n; c += kTkThreads) {
-    if (!s_keep[c] || s_pos[c] >= a.n_nodes) continue;
-    const int i = s_pos[c];
+  if (keep && pos < a.n_nodes) {
+    const int i = pos;
     const int par = a.c_par[cb + c];
     a.out_tok[(long)b * a.n_nodes + i] = a.c_tok[cb + c];
     // (the parent scores at least as high and comes earlier: it is kept too)
     a.out_par[(long)b * a.n_nodes + i] = par >= 0 ? (s_keep[par] ? s_pos[par] : -2) : -1;
     if (a.out_score) a.out_score[(long)b * a.n_nodes + i] = s_sc[c];
   }
-  for (int i = N + tid; i < a.n_nodes; i += kTkThreads) {
+  for (int i = N + c; i < a.n_nodes; i += kMaxCand) {
     a.out_tok[(long)b * a.n_nodes + i] = -1;
     a.out_par[(long)b * a.n_nodes + i] = -2;
     if (a.out_score) a.out_score[(long)b * a.n_nodes + i] = -INFINITY;
   }
-}
-
-void launch_tree_topk(const TreeArgs& a, int rows, hipStream_t st) {
-  hipLaunchKernelGGL(k_tree_topk, dim3(rows, kTkBlocks), dim3(kTkThreads), 0, st, a);
 }
 
 void launch_tree_step(const TreeArgs& a, hipStream_t st) {
@@ -410,7 +331,7 @@ void launch_tree_step(const TreeArgs& a, hipStream_t st) {
 }
 
 void launch_tree_final(const TreeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_tree_final, dim3(a.B), dim3(kTkThreads), 0, st, a);
+  hipLaunchKernelGGL(k_tree_final, dim3(a.B), dim3(kMaxCand), 0, st, a);
 }
 
 }  // namespace osp
