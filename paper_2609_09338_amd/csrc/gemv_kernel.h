@@ -32,6 +32,9 @@
 #include "internal.h"
 #include "pick.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace osp {
 
 constexpr int kGemvThreads = 256;
@@ -320,7 +323,11 @@ k_gemv(GemvArgs a, int rows_per_wave) {
     if (n_lo >= a.N) return;
   }
 
-  for (int r0 = 0; r0 < rows; r0 += RB) {
+  // Groups of RB rows are dealt to grid y (the weights, read again by each group, come from
+  // L2): walked one after another by the same wavefronts, the 16 groups of a 128-token fp32
+  // prompt made the launch a chain of as many round trips (QKV of d 256 165 -> 16 us, taps of
+  // 1536 columns 75 -> 10 us).
+  for (int r0 = RB * blockIdx.y; r0 < rows; r0 += RB * gridDim.y) {
     float xc[RB][XV][VEC];                     // this lane's input values (cached mode)
     float inv_rms[RB];
 #pragma unroll
@@ -566,10 +573,13 @@ k_gemv(GemvArgs a, int rows_per_wave) {
 // row in one step ({1, 2, 4, 8}, RB * XV <= 8 so the cached input is <= 64 values);
 // NW weight rows per step with NW * XV * RB <= 8 vectors in flight per lane (SwiGLU
 // counts gate and up) so that 4 wavefronts fit per SIMD; NW shrinks further until
-// the grid has enough wavefronts.
+// the grid has enough wavefronts.  Projections of more than 8 rows take up to 32 sums per
+// lane instead: a wavefront reads its 8 input rows (and, normalising, sums their squares)
+// once per step, which bounds it there, not the weights.
 struct GemvPlan {
-  int rb, xv, nw, rpw, waves;
+  int rb, xv, nw, rpw, waves, groups;
 };
+constexpr int kGemvMaxGroups = 1024;   // grid y; further row groups are walked
 
 inline GemvPlan gemv_plan(int wdtype, EpiKind epi, int rows, int N, int Kd) {
   GemvPlan p;
@@ -580,10 +590,12 @@ inline GemvPlan gemv_plan(int wdtype, EpiKind epi, int rows, int N, int Kd) {
   while (xv < per_lane && xv * 2 * p.rb <= 8) xv *= 2;
   p.xv = xv;
   const int f = epi == EPI_SWIGLU ? 2 : 1;
-  int nw = 8;
-  while (nw > 1 && nw * xv * p.rb * f > 8) nw /= 2;
+  p.groups = std::min((rows + p.rb - 1) / p.rb, kGemvMaxGroups);
+  const int most = rows > 8 && epi != EPI_LOGITS ? 32 : 8;
+  int nw = most == 32 ? 4 : 8;
+  while (nw > 1 && nw * xv * p.rb * f > most) nw /= 2;
   const int min_waves = epi == EPI_LOGITS ? 1024 : 2048;
-  while (nw > 1 && (N + nw - 1) / nw < min_waves) nw /= 2;
+  while (nw > 1 && (long)((N + nw - 1) / nw) * (most == 32 ? p.groups : 1) < min_waves) nw /= 2;
   p.nw = nw;
   int rpw = (N + kGemvMaxWaves - 1) / kGemvMaxWaves;
   rpw = (rpw + nw - 1) / nw * nw;
@@ -593,19 +605,20 @@ inline GemvPlan gemv_plan(int wdtype, EpiKind epi, int rows, int N, int Kd) {
 }
 
 template <typename TW, int SRC, int EPI, int RB, int NW, int XV>
-void launch_gemv_t(const GemvArgs& a, int rpw, hipStream_t st) {
+void launch_gemv_t(const GemvArgs& a, const GemvPlan& p, hipStream_t st) {
+  const int rpw = p.rpw;
   const int waves = (a.N + rpw - 1) / rpw;
-  const int grid = (waves + kGemvWavesPerBlock - 1) / kGemvWavesPerBlock;
+  const dim3 grid((waves + kGemvWavesPerBlock - 1) / kGemvWavesPerBlock, p.groups);
   const bool cached = a.Kd / Vec<TW>::N <= OSP_WAVE * XV;
   if constexpr (SRC == SRC_ATTN) {
     // (only the cached form exists: gemv_attn_supported bounds Kd)
-    hipLaunchKernelGGL((k_gemv<TW, SRC, EPI, RB, NW, XV, true>), dim3(grid), dim3(kGemvThreads), 0, st, a, rpw);
+    hipLaunchKernelGGL((k_gemv<TW, SRC, EPI, RB, NW, XV, true>), grid, dim3(kGemvThreads), 0, st, a, rpw);
   } else {
     if (cached)
-      hipLaunchKernelGGL((k_gemv<TW, SRC, EPI, RB, NW, XV, true>), dim3(grid), dim3(kGemvThreads), 0,
+      hipLaunchKernelGGL((k_gemv<TW, SRC, EPI, RB, NW, XV, true>), grid, dim3(kGemvThreads), 0,
                          st, a, rpw);
     else
-      hipLaunchKernelGGL((k_gemv<TW, SRC, EPI, RB, NW, XV, false>), dim3(grid), dim3(kGemvThreads), 0,
+      hipLaunchKernelGGL((k_gemv<TW, SRC, EPI, RB, NW, XV, false>), grid, dim3(kGemvThreads), 0,
                          st, a, rpw);
   }
 }
@@ -613,10 +626,14 @@ void launch_gemv_t(const GemvArgs& a, int rpw, hipStream_t st) {
 template <typename TW, int SRC, int EPI, int RB, int XV>
 void launch_gemv_nw(const GemvPlan& p, const GemvArgs& a, hipStream_t st) {
   constexpr int F = (EPI == EPI_SWIGLU) ? 2 : 1;
-  if constexpr (8 * XV * RB * F <= 8) { if (p.nw == 8) return launch_gemv_t<TW, SRC, EPI, RB, 8, XV>(a, p.rpw, st); }
-  if constexpr (4 * XV * RB * F <= 8) { if (p.nw == 4) return launch_gemv_t<TW, SRC, EPI, RB, 4, XV>(a, p.rpw, st); }
-  if constexpr (2 * XV * RB * F <= 8) { if (p.nw == 2) return launch_gemv_t<TW, SRC, EPI, RB, 2, XV>(a, p.rpw, st); }
-  return launch_gemv_t<TW, SRC, EPI, RB, 1, XV>(a, p.rpw, st);
+  if constexpr (RB == 8 && EPI != EPI_LOGITS && std::is_same<TW, float>::value) {
+    if constexpr (F == 1) { if (p.nw == 4) return launch_gemv_t<TW, SRC, EPI, RB, 4, XV>(a, p, st); }
+    if (p.nw == 2) return launch_gemv_t<TW, SRC, EPI, RB, 2, XV>(a, p, st);
+  }
+  if constexpr (8 * XV * RB * F <= 8) { if (p.nw == 8) return launch_gemv_t<TW, SRC, EPI, RB, 8, XV>(a, p, st); }
+  if constexpr (4 * XV * RB * F <= 8) { if (p.nw == 4) return launch_gemv_t<TW, SRC, EPI, RB, 4, XV>(a, p, st); }
+  if constexpr (2 * XV * RB * F <= 8) { if (p.nw == 2) return launch_gemv_t<TW, SRC, EPI, RB, 2, XV>(a, p, st); }
+  return launch_gemv_t<TW, SRC, EPI, RB, 1, XV>(a, p, st);
 }
 
 template <typename TW, int SRC, int EPI, int RB>

@@ -27,6 +27,10 @@ CASES = {
     "wide_taps": ("p_wide_taps", [(0, 65), (3, 2), (64, 63)]),
     "f32": ("p_tiny_f32", [(0, 65)]),
     "f32_turn": ("p_tiny_f32", [(70, 3)]),
+    # fp32 products go by groups of eight rows
+    "f32_group": ("p_tiny_f32", [(0, 8)]),
+    "f32_two_groups": ("p_f32_two_layers", [(3, 1), (0, 8)]),
+    "f32_groups": ("p_f32_two_layers", [(0, 100), (20, 33)]),
 }
 
 
@@ -40,7 +44,12 @@ def test_prompt_matches_oracle(name, K):
     from paper_2609_09338_amd.binding import Drafter, make_config
     body, seqs = CASES[name]
     # (taps of 3 x 200 columns: not a whole number of 32-column steps)
-    w = synth.get("p_qwen_small").with_(target_hidden=200) if body == "p_odd_taps" else synth.get(body)
+    if body == "p_odd_taps":
+        w = synth.get("p_qwen_small").with_(target_hidden=200)
+    elif body == "p_f32_two_layers":
+        w = synth.get("p_tiny_f32").with_(n_layers=2)
+    else:
+        w = synth.get(body)
     w = w.with_(name="prompt_" + name, batch=len(seqs), K=max(K, 1), temps=(0.0,), draft_temps=())
     weights, d2t = synth.make_weights(w), synth.make_d2t(w)
     dr_o = OH.build_drafter(w, weights, d2t)
