@@ -173,18 +173,24 @@ int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st
 bool gemm_use_mfma(int wdtype, int rows);
 int gemm_rows_per_block(EpiKind epi);
 
-// LM head on the matrix cores for 1..64 rows per pass (inputs: RMSNorm_final(x),
+// LM head on the matrix cores for 1..96 rows per pass (inputs: RMSNorm_final(x),
 // rows gathered through `gather`).  One softmax record
 // per wavefront and row covers blk_rows consecutive logits; nblk records per row.
 struct LmPlan {
-  int mt;        // M tiles of 16 rows
   int grid;      // blocks
   int T;         // 16-row weight tiles per wavefront
   int nblk;      // records per row
   int blk_rows;  // logits per record (16 T)
 };
 constexpr int kLmMaxRows = 64;
-LmPlan lm_head_plan(int rows, int N, int n_cu);
+constexpr int kSkMaxRows = 96;   // rows of the widest streaming pass
+// Rows of the head's next pass when `left` are to come.  The head (d 1024, 152k rows) takes
+// 71 us for 64 rows and 89 for 96: 65 to 96 rows go in one pass instead of two, 97 to
+// 128 in two of 64, more by 96.
+inline int lm_pass_rows(int left) {
+  return left <= kSkMaxRows ? left : (left <= 2 * kLmMaxRows ? kLmMaxRows : kSkMaxRows);
+}
+LmPlan lm_head_plan(int N, int n_cu);
 // The head's weights a.w0 are the packed copy that launch_pack_head writes, of the
 // [N][Kd] bf16 matrix with N = a.N and Kd = a.Kd.
 // norm_in: inputs are the fp32 rows xin (ldx, gathered), normalised with gamma / eps
@@ -201,7 +207,8 @@ bool launch_lm_head(const GemvArgs& a, const LmPlan& p, bool norm_in, hipStream_
 long packed_head_bytes(int N, int Kd);
 void launch_pack_head(const void* w, int N, int Kd, void* packed, hipStream_t st);
 
-// Projections of passes of at most kLmMaxRows rows on the same streaming kernel:
+// Projections of passes of at most kLmMaxRows rows (SRC_PREP: kSkMaxRows) on the same
+// streaming kernel:
 // src SRC_PREP (pairs; [xs ; xa] when seg > 0), SRC_TAPS, or SRC_SWIGLU (the down
 // projection forms silu(gate) * up from the gate/up partials itself); with w1 set, the up
 // matrix supplies rows [N, 2N).  Writes K-split partial sums to

@@ -50,8 +50,8 @@ enum SkSrc { SK_PREP = 0, SK_NORM = 1, SK_TAPS = 2, SK_SWIGLU = 3, SK_ATTN = 4 }
 enum SkEpi { SK_LOGITS = 0, SK_PART = 1 };
 
 // Input columns resident per block and phase: 64 rows x 512 or 32 rows x 1024
-// columns of hi / lo pairs fill 132 KB of LDS.
-template <int MT> struct SkCfg { static constexpr int KC = MT == 4 ? 512 : 1024; };
+// columns of hi / lo pairs fill 132 KB of LDS, 96 rows x 256 columns 104 KB.
+template <int MT> struct SkCfg { static constexpr int KC = MT == 6 ? 256 : (MT == 4 ? 512 : 1024); };
 
 // T: tiles per wavefront (LM head); kc: K columns per block (projections, a multiple
 // of 256 up to KC).
@@ -67,8 +67,8 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
   constexpr int TMAX = EPI == SK_LOGITS ? kSkTmaxHead : kSkTmaxProj;
   constexpr int NU = TMAX * NCH;          // units per phase (bound)
   constexpr bool EXACT = SRC == SK_TAPS;  // bf16 inputs: no lo part
-  // ring depth: 64-row passes hold 80 accumulators and need the registers
-  constexpr int kSkDepth = MT == 4 ? 2 : kSkDepthMax;
+  // ring depth: passes of 64 (96) rows hold 80 (120) accumulators and need the registers
+  constexpr int kSkDepth = MT >= 4 ? 2 : kSkDepthMax;
   __shared__ __attribute__((aligned(16))) bf16_t xh[ROWS * PITCH];
   __shared__ __attribute__((aligned(16))) bf16_t xl[EXACT ? 8 : ROWS * PITCH];
 
@@ -89,9 +89,9 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
   const int ntiles = max(0, min(min(T, TMAX), nt16 - t0));
   const int k_lo = EPI == SK_PART ? blockIdx.y * kc : 0;
   const int k_hi = EPI == SK_PART ? min(a.Kd, k_lo + kc) : a.Kd;
-  // units per tile and phase (attention outputs: one 256-column unit, a constant, so that
+  // units per tile and phase (96 rows: phases of one unit; attention outputs: one 256-column unit, a constant, so that
   // the prefetch below is known to be a single unit)
-  const int nch = EPI == SK_PART ? (SRC == SK_ATTN ? 1 : kc / kSkUnit) : NCH;
+  const int nch = EPI == SK_PART && MT < 6 ? (SRC == SK_ATTN ? 1 : kc / kSkUnit) : NCH;
   // LM head blocks with no tile at all leave at once (block-uniform, before any barrier)
   if (EPI == SK_LOGITS && blockIdx.x * kSkWaves * T >= nt16) return;
 
@@ -190,10 +190,12 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
     dmap[j] = EPI == SK_LOGITS ? a.d2t[min((t0 + j) * 16 + wrow, a.N - 1)] : 0;
   // ... and the temperatures of the lane's output rows 16 mt + 4 grp + e (row r of the
   // pass is sequence r), requested now so that the epilogue does not wait for them
+  // (96 rows: read there, to hold no registers during the stream)
   constexpr int NTK = EPI == SK_LOGITS ? 4 * MT : 1;
+  constexpr bool kTkEarly = MT <= 4;
   float tk[NTK];
 #pragma unroll
-  for (int k = 0; k < NTK; ++k)
+  for (int k = 0; k < NTK && kTkEarly; ++k)
     tk[k] = EPI == SK_LOGITS ? a.temp[min((k / 4) * 16 + 4 * grp + (k % 4), R - 1)] : 0.f;
   if constexpr (SRC == SK_NORM) {
     // RMS of the row (wavefront sums, then the block's in a fixed order), then the
@@ -242,12 +244,12 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
     //      Rows past R are left as they are: they only feed outputs that are dropped.
     //      Each thread requests a batch of 16-byte pieces before storing any, so the
     //      copy costs a round trip or two instead of one per piece ------------------------
-    const int span8 = (EPI == SK_PART ? kc : KC) / 8;      // 16-byte pieces per row
+    const int span8 = (EPI == SK_PART && MT < 6 ? kc : KC) / 8;      // 16-byte pieces per row
     const int nitems = R * span8;
     // (the LM head holds 20 MT accumulators: smaller batches for more rows)
     // (SwiGLU inputs, at most 16 rows: one piece per thread at the usual K range, each
     // piece kSwRound splits' loads)
-    constexpr int BATCH = EPI == SK_LOGITS ? (MT == 4 ? 1 : (MT == 2 ? 2 : 4)) : (SRC == SK_SWIGLU ? 1 : 4);
+    constexpr int BATCH = EPI == SK_LOGITS ? (MT >= 4 ? 1 : (MT == 2 ? 2 : 4)) : (SRC == SK_SWIGLU ? 1 : 4);
     constexpr int kSwRound = 4;
     if constexpr (SRC == SK_ATTN) {
       // Attention outputs (K range of one 256-column unit: 32 pieces per row, MT pieces
@@ -447,26 +449,31 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
           const sk_bf16x8 bw = *reinterpret_cast<const sk_bf16x8*>(&w[ks]);
-          // all A fragments of this K step are requested before the first product, so
-          // one LDS latency covers the step's 2 MT products instead of one each
-          sk_bf16x8 ah[MT], al[MT];
+          // all A fragments of this K step (96 rows: of three M tiles) are requested before
+          // the first product, so one LDS latency covers their products instead of one each
+          constexpr int MG = MT == 6 ? 3 : MT;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            // (the single normalised row: every lane reads row 0 at its column in the
-            // whole row; the outputs of rows 1..15 are dropped)
-            const int off = SRC == SK_NORM ? k0 + kl + 32 * ks : (mt * 16 + wrow) * PITCH + kl + 32 * ks;
-            ah[mt] = *reinterpret_cast<const sk_bf16x8*>(xh + off);
-            if constexpr (!EXACT) al[mt] = *reinterpret_cast<const sk_bf16x8*>(xl + off);
-          }
+          for (int m0 = 0; m0 < MT; m0 += MG) {
+            sk_bf16x8 ah[MG], al[MG];
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            acc[j][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bw, acc[j][mt], 0, 0, 0);
-            if constexpr (!EXACT) acc[j][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bw, acc[j][mt], 0, 0, 0);
+            for (int mt = 0; mt < MG; ++mt) {
+              // (the single normalised row: every lane reads row 0 at its column in the
+              // whole row; the outputs of rows 1..15 are dropped)
+              const int off = SRC == SK_NORM ? k0 + kl + 32 * ks : ((m0 + mt) * 16 + wrow) * PITCH + kl + 32 * ks;
+              ah[mt] = *reinterpret_cast<const sk_bf16x8*>(xh + off);
+              if constexpr (!EXACT) al[mt] = *reinterpret_cast<const sk_bf16x8*>(xl + off);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MG; ++mt) {
+              sk_f32x4& c = acc[j][m0 + mt];
+              c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bw, c, 0, 0, 0);
+              if constexpr (!EXACT) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bw, c, 0, 0, 0);
+            }
+            // keep that order: the scheduler, near the register limit, would otherwise
+            // put a wait on each read right before its product
+            __builtin_amdgcn_sched_group_barrier(0x100, EXACT ? MG : 2 * MG, 0);   // LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x008, EXACT ? MG : 2 * MG, 0);   // MFMAs
           }
-          // keep that order: the scheduler, near the register limit, would otherwise
-          // put a wait on each read right before its product
-          __builtin_amdgcn_sched_group_barrier(0x100, EXACT ? MT : 2 * MT, 0);   // LDS reads
-          __builtin_amdgcn_sched_group_barrier(0x008, EXACT ? MT : 2 * MT, 0);   // MFMAs
         }
       }
     }
@@ -498,7 +505,12 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
     // its rows and merges the partner's copies of them, so V rows cost about V
     // shuffles instead of 4 V.
     constexpr int V = 4 * MT;
-    constexpr int NH = V == 16 ? 4 : (V == 8 ? 3 : 2);    // halving steps (then plain)
+    constexpr int NH = V == 16 ? 4 : (V >= 8 ? 3 : 2);    // halving steps (then plain)
+    constexpr int REM = V >> NH;                          // rows a lane ends with (96: 3)
+    if constexpr (!kTkEarly) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) tk[k] = a.temp[min((k / 4) * 16 + 4 * grp + (k % 4), R - 1)];
+    }
     // masked logits (written here, after the stream: stores issued between the ring's
     // loads would lengthen every wait on them).  Conditions that hold for the whole
     // wavefront (every row of the pass present, a tile inside the vocabulary) are taken
@@ -523,7 +535,7 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               float* dst = yc + (long)(mt * 16 + e) * a.ld_logits;
-              if constexpr (MT == 4) __builtin_nontemporal_store(acc[j][mt][e], dst);
+              if constexpr (MT >= 4) __builtin_nontemporal_store(acc[j][mt][e], dst);
               else *dst = acc[j][mt][e];
             }
         } else {
@@ -533,7 +545,7 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
             for (int e = 0; e < 4; ++e) {
               float* dst = yc + (long)(mt * 16 + e) * a.ld_logits;
               if (mt * 16 + 4 * grp + e < R && n < a.N) {
-                if constexpr (MT == 4) __builtin_nontemporal_store(acc[j][mt][e], dst);
+                if constexpr (MT >= 4) __builtin_nontemporal_store(acc[j][mt][e], dst);
                 else *dst = acc[j][mt][e];
               }
             }
@@ -572,12 +584,15 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
           ri[i] = take ? pi : mi;
         }
       } else {
-        const float pv = xor_lane_c(rv[0], mask);
-        const int pi = xor_lane_ci(ri[0], mask);
-        if (pv > rv[0] || (pv == rv[0] && pi < ri[0])) { rv[0] = pv; ri[0] = pi; }
+#pragma unroll
+        for (int i = 0; i < REM; ++i) {
+          const float pv = xor_lane_c(rv[i], mask);
+          const int pi = xor_lane_ci(ri[i], mask);
+          if (pv > rv[i] || (pv == rv[i] && pi < ri[i])) { rv[i] = pv; ri[i] = pi; }
+        }
       }
     }
-    // lane p of the group now holds row k(p) = its top NH bits, read as a number
+    // lane p of the group now holds rows REM k(p) + i, k(p) = its top NH bits, read as a number
     auto row_of_lane = [&](int p) {
       int k = 0;
 #pragma unroll
@@ -587,14 +602,14 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
     auto lane_of_row = [&](int k) {
       int p = 0;
 #pragma unroll
-      for (int st = 0; st < NH; ++st) p |= ((k >> (NH - 1 - st)) & 1) << (3 - st);
+      for (int st = 0; st < NH; ++st) p |= ((k / REM >> (NH - 1 - st)) & 1) << (3 - st);
       return p;
     };
     // (2) every lane fetches the maxima of its V rows and sums its own columns
     float sv[V];
 #pragma unroll
     for (int k = 0; k < V; ++k) {
-      const float Mk = row_lane_c(rv[0], lane_of_row(k));
+      const float Mk = row_lane_c(rv[k % REM], lane_of_row(k));
       const int m = (k / 4) * 16 + 4 * grp + (k % 4);
       const float Tk = m < R ? tk[k] : 0.f;
       // (masked entries add exp(-inf) = 0; a row with no sum -- T = 0, or every entry
@@ -622,29 +637,32 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
           sv[i] = mv + xor_lane_c(ov, mask);
         }
       } else {
-        sv[0] += xor_lane_c(sv[0], mask);
+#pragma unroll
+        for (int i = 0; i < REM; ++i) sv[i] += xor_lane_c(sv[i], mask);
       }
     }
     if ((lane & ((16 >> NH) - 1)) == 0) {
-      const int k = row_of_lane(lane & 15);
-      const int m = (k / 4) * 16 + 4 * grp + (k % 4);
-      if (m < R) {
-        float* p = a.part + ((long)m * a.nblk + wg) * 4;
-        p[0] = rv[0];
-        p[1] = sv[0];
-        p[2] = __int_as_float(rv[0] > -INFINITY ? ri[0] : -1);
-        p[3] = 0.f;
+#pragma unroll
+      for (int i = 0; i < REM; ++i) {
+        const int k = REM * row_of_lane(lane & 15) + i;
+        const int m = (k / 4) * 16 + 4 * grp + (k % 4);
+        if (m < R) {
+          float* p = a.part + ((long)m * a.nblk + wg) * 4;
+          p[0] = rv[i];
+          p[1] = sv[i];
+          p[2] = __int_as_float(rv[i] > -INFINITY ? ri[i] : -1);
+          p[3] = 0.f;
+        }
       }
     }
   }
 }
 
-static int sk_mt(int rows) { return rows <= 16 ? 1 : (rows <= 32 ? 2 : 4); }
+static int sk_mt(int rows) { return rows <= 16 ? 1 : (rows <= 32 ? 2 : (rows <= 64 ? 4 : 6)); }
 
 // ---- LM head ----------------------------------------------------------------------------
-LmPlan lm_head_plan(int rows, int N, int n_cu) {
+LmPlan lm_head_plan(int N, int n_cu) {
   LmPlan p;
-  p.mt = sk_mt(rows);
   const int nt16 = (N + 15) / 16;
   // one block per CU (the register budget allows 2 wavefronts per SIMD)
   p.grid = std::min(n_cu, kGemvMaxWaves / kSkWaves);
@@ -662,7 +680,9 @@ template <int SRC, int EPI>
 static void sk_launch(int mt, dim3 grid, const GemvArgs& a, int T, int kc, hipStream_t st) {
   if (mt == 1) hipLaunchKernelGGL((k_skinny<1, SRC, EPI>), grid, dim3(kSkThreads), 0, st, a, T, kc);
   else if (mt == 2) hipLaunchKernelGGL((k_skinny<2, SRC, EPI>), grid, dim3(kSkThreads), 0, st, a, T, kc);
-  else hipLaunchKernelGGL((k_skinny<4, SRC, EPI>), grid, dim3(kSkThreads), 0, st, a, T, kc);
+  else if (mt == 6) {
+    if constexpr (SRC == SK_PREP) hipLaunchKernelGGL((k_skinny<6, SRC, EPI>), grid, dim3(kSkThreads), 0, st, a, T, kc);
+  } else hipLaunchKernelGGL((k_skinny<4, SRC, EPI>), grid, dim3(kSkThreads), 0, st, a, T, kc);
 }
 
 bool lm_head_norm_in_supported(int rows, int Kd) { return rows == 1 && Kd <= 8 * kSkThreads; }
@@ -672,7 +692,7 @@ bool launch_lm_head(const GemvArgs& a, const LmPlan& p, bool norm_in, hipStream_
   // 8 x kSkThreads columns; anything else is refused (nothing launched)
   if (norm_in && !lm_head_norm_in_supported(a.max_rows, a.Kd)) return false;
   if (norm_in) sk_launch<SK_NORM, SK_LOGITS>(1, dim3(p.grid), a, p.T, 0, st);
-  else sk_launch<SK_PREP, SK_LOGITS>(p.mt, dim3(p.grid), a, p.T, 0, st);
+  else sk_launch<SK_PREP, SK_LOGITS>(sk_mt(a.max_rows), dim3(p.grid), a, p.T, 0, st);
   return true;
 }
 
@@ -681,6 +701,8 @@ bool launch_lm_head(const GemvArgs& a, const LmPlan& p, bool norm_in, hipStream_
 // unit) until the grid holds about 256 blocks: each wavefront then waits on few loads,
 // and the launch costs about one load round trip instead of a per-wavefront stream.
 static int skinny_kc(int rows, int N2, int Kd) {
+  // (more than 64 rows: one-unit phases, as few to a block as kMaxKSplit ranges allow)
+  if (rows > kLmMaxRows) return kSkUnit * (((Kd + kSkUnit - 1) / kSkUnit + kMaxKSplit - 1) / kMaxKSplit);
   const int KC = rows > 32 ? SkCfg<4>::KC : SkCfg<1>::KC;
   const int nb = (((N2 + 15) / 16) + kSkWaves - 1) / kSkWaves;   // blocks per K range
   int kc = KC;

@@ -222,6 +222,16 @@ def test_short_chains_match_oracle(name, K):
     _run_parity(w, 3, list(range(w.batch)), tol)
 
 
+@pytest.mark.parametrize("batch", [10, 13, 14, 19])
+def test_blocks_of_many_rows_match_oracle(batch):
+    """Passes of 65 to 96 rows (70, 91: one pass of the streaming head and products) and of
+    more (98: heads of 64 + 34 rows; 133: 96 + 37, tiled products), at sequences on the
+    passes' first and last rows."""
+    _require_gpu()
+    w = synth.get("p_block").with_(name=f"p_block_b{batch}", batch=batch)
+    _run_parity(w, 2, sorted({0, 9, min(13, batch - 1), batch - 1}), 2e-2)
+
+
 def test_tiny_fp32_variants_match_oracle():
     """The small fp32 chain draft: zero and N(0, 0.02) expansion, greedy and T = 1,
     noise sigma 0.5 and 2 (8 runs)."""
