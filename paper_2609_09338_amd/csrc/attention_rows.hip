@@ -16,8 +16,9 @@
 //     when the K index runs over tokens 4 g .. 4 g + 3 of both pages of a pair, so
 //     nothing moves between lanes but the row maxima and sums;
 //   * key rows are stored with their 16-byte pieces permuted by the token, so that the
-//     16 rows a fragment read touches fall into different banks.  Value pages are read
-//     in the order they are stored.
+//     16 rows a fragment read touches fall into different banks.  Value pages are stored
+//     in pairs, the four tokens of a lane's K index from both pages side by side: one read
+//     and no register moves per value fragment.
 // The matrix cores bound it (four products per score and value, hi and lo): registers
 // hold two wavefronts per SIMD, so one's softmax overlaps another's products.
 // Blocks are (kv head, row tile and sequence, context split): heads go to the XCDs in
@@ -28,6 +29,9 @@
 // Measured per layer: one 1999-token prompt (16 / 8 heads x 128) 1422 -> 78 us; four of 8200
 // tokens in all (32 / 8 heads x 128) 5850 -> 586 us; two turns of 770 tokens over 6000-8000
 // cached positions (16 / 8 x 128) 672 -> 216 us; a 17-row block (32 / 8 x 64) 24.2 -> 12.3 us.
+// Page-table entries ahead of the loop and values in pairs: the two turns' call 598 -> 585 us.
+// (rocprofv3, the two turns: matrix cores busy 23% of the time, 3.4 vector instructions per
+// product; on average one wavefront per SIMD of the two that fit.)
 #include "common.h"
 #include "internal.h"
 
@@ -122,10 +126,14 @@ __global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles) {
 
   // ---- staging: wavefront w brings page w of a step -----------------------------------------
   ar_u32x4 kr[LD], vr[LD];
+  // the wavefront's page-table entries of 64 steps, one per lane (a scalar load per step
+  // would stand between the step's start and its page requests); pages past the positions
+  // read the last one again and are cleared in put
+  const int pg_last = max((p_hi - 1) / kArPage, 0);
+  int ent = 0;
   auto request = [&](int t) {
-    const int pg = p_lo / kArPage + 4 * t + wave;
-    // (a page past the positions reads page 0 of the pool and is cleared in put)
-    const long base = (pg * kArPage < p_hi ? (long)bt[pg] : 0) * blk_elems;
+    if ((t & 63) == 0) ent = bt[min(p_lo / kArPage + 4 * (t + lane) + wave, pg_last)];
+    const long base = (long)__builtin_amdgcn_readlane(ent, t & 63) * blk_elems;
     const ar_u32x4* kp = reinterpret_cast<const ar_u32x4*>(kvb + base + k_off);
     const ar_u32x4* vp = reinterpret_cast<const ar_u32x4*>(kvb + base + v_off);
 #pragma unroll
@@ -149,7 +157,11 @@ __global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles) {
       const int x = i * 64 + lane;
       const int tok = x / KROW, c = x % KROW;
       sk[buf][(wave * kArPage + tok) * KROW + (c ^ (tok & (KROW - 1)))] = kr[i];
-      sv[buf][wave * PIECES + x] = vr[i];
+      // values: tokens 4 g .. 4 g + 3 of a dimension beside those of the pair's other page,
+      // the order in which the second product takes them
+      uint2* v2 = reinterpret_cast<uint2*>(sv[buf]) + (((wave >> 1) * HD + (x >> 1)) * 4 + 2 * (x & 1)) * 2 + (wave & 1);
+      v2[0] = make_uint2(vr[i][0], vr[i][1]);
+      v2[2] = make_uint2(vr[i][2], vr[i][3]);
     }
   };
 
@@ -222,14 +234,11 @@ __global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles) {
       }
     }
     // O^T[dim][query] += V^T P^T over page pairs
-    const uint2* v2 = reinterpret_cast<const uint2*>(sv[buf]);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
       for (int n = 0; n < NT; ++n) {
-        const uint2 x = v2[(2 * i) * PIECES * 2 + (16 * n + row) * 4 + grp];
-        const uint2 y = v2[(2 * i + 1) * PIECES * 2 + (16 * n + row) * 4 + grp];
-        const ar_bf16x8 va = __builtin_bit_cast(ar_bf16x8, make_uint4(x.x, x.y, y.x, y.y));
+        const ar_bf16x8 va = __builtin_bit_cast(ar_bf16x8, sv[buf][(i * HD + 16 * n + row) * 4 + grp]);
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
           acc[q][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, ph[q][i], acc[q][n], 0, 0, 0);

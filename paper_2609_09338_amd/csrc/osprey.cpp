@@ -393,11 +393,12 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
 }
 
 // Context splits of a pass whose attention runs by blocks of query vectors: none while
-// the tiles of vectors give the chip four blocks per CU by themselves (two run at once;
-// causal tiles differ in length, so the rest balances them); else as many pieces of at
-// least kRowSplitLen positions as reach that.  Whole calls with 1 / 2 / 4 blocks per CU:
-// a 1999-token prompt 775 / 762 / 742 us, two turns of 770 tokens over 7000 positions
-// 1011 / 914 / 864 us.
+// the tiles of vectors give the chip three and a half blocks per CU by themselves (two run
+// at once; causal tiles differ in length, so the rest balances them); else as many pieces of
+// at least kRowSplitLen positions as stay below that.  Whole calls with 1 / 2 / 3 / 4 / 6 / 8
+// splits: a 1999-token prompt (256 tiles) 480 / 473 / 461 / 468 / 465 / 470 us, two turns of
+// 770 tokens over 7000 positions (104) 754 / 643 / 588 / 601 / 580 / 585, four prompts of
+// 3600 tokens (450) 649 / 680 / 676 / 684 / 687 / 699.
 constexpr long kRowSplitLen = 128;
 SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, int rows_per_seq, int rows,
                           int max_split) {
@@ -407,7 +408,7 @@ SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, in
   // a batch's tiles: the longest sequence's, and no more than its rows fill
   const int per_seq = attn_rows_tiles(rows_per_seq, group);
   const long tiles = std::min<long>((long)B * per_seq, (long)attn_rows_tiles(rows, group) + B);
-  long n = 4L * h->n_cu / (tiles * c.n_kv_heads);
+  long n = 7L * h->n_cu / (2 * tiles * c.n_kv_heads);
   n = std::max<long>(1, std::min<long>(std::min<long>(n, max_split), ctx / kRowSplitLen));
   SplitPlan p = sp;
   long len = ((ctx + n - 1) / n + 63) / 64 * 64;
