@@ -4,20 +4,22 @@
 // The kernel of gemm_mfma.h gives every 64 rows a block of their own, whose weights go
 // straight from memory to registers, and splits K into 256-column pieces whatever the
 // size: at thousands of rows each weight is read once per 64 rows and 8-16 partial sums
-// of every output pass through memory.  Here a block computes 128 rows x 256 weight rows
-// (a wavefront 64 x 128), and K is split only as far as it takes to give every CU two
-// blocks.  Per 32 columns a block copies 16 KB of inputs (hi, lo) and 16 KB of weights
-// straight into LDS (buffer loads to LDS, no registers) while it multiplies the 32
-// columns before; a wavefront reads 16 fragments from LDS for 64 products, about half of
-// what the LDS delivers in that time.  Two blocks per CU (64 KB of LDS, 2 wavefronts per
-// SIMD) cover each other's barriers.  16-byte pieces are permuted within a row by the
-// row, so that the 16 rows of a fragment read fall into different banks.
+// of every output pass through memory.  Here a block computes 128 or 256 rows x 256 weight
+// rows (a wavefront 64 x 128), and K is split only as far as it takes to fill the chip.  Per
+// 32 columns a block copies its inputs (hi, lo) and 16 KB of weights straight into LDS
+// (buffer loads to LDS, no registers) while it multiplies earlier columns; a wavefront reads
+// 16 fragments from LDS for 64 products, about half of what the LDS delivers in that time.
+// 128-row blocks run two to a CU with two stages each (64 KB of LDS, 2 wavefronts per SIMD)
+// and cover each other's barriers, but a copy has one step to arrive; 256-row blocks have the
+// CU to themselves, three stages (144 KB), and wait only for copies requested two steps
+// before.  16-byte pieces are permuted within a row by the row, so that the 16 rows of a
+// fragment read fall into different banks.
 //
 // The weights are the A operand, so a lane ends with four consecutive output columns of
 // one row: float4 stores of partial sums, and for gate/up (a wavefront holds the gate and
 // the up tile of the same columns) silu(g) u in registers, written as the down
 // projection's hi / lo input without the row kernel and its 2 x 2 F floats per row.
-// Blocks go to the XCDs in contiguous ranges of tiles, eight row tiles by rising weight
+// Blocks go to the XCDs in contiguous ranges of tiles, 1024 rows by rising weight
 // tile, so that an XCD's blocks share inputs and weights in its L2.
 // Bound by the matrix cores (two products per weight: hi and lo inputs).  Measured, before
 // and after: gate/up of 8200 rows (2 x 9728 x 2560) 4256 us and 1358 us of SwiGLU rows ->
@@ -35,11 +37,11 @@ typedef __bf16 gr_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float gr_f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned gr_u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGrM = 128;        // input rows per block
+constexpr int kGrM = 64;         // input rows per wavefront (two or four wavefronts of a block)
 constexpr int kGrN = 256;        // weight rows per block
 constexpr int kGrK = 32;         // columns per step
 constexpr int kGrP = kGrK / 8;   // 16-byte pieces per row and step
-constexpr int kGrGroup = 8;      // row tiles walked together
+constexpr int kGrGroup = 1024;   // rows walked together
 constexpr int kGrXcd = 8;
 
 // Where piece c of row r of a tile lies: four pieces per 64-byte row, permuted so that the
@@ -52,23 +54,29 @@ OSP_DEV void gr_copy(const void* base, gr_u32x4* lds, int voffset, int soffset) 
                                            0, 0);
 }
 
-template <int SRC, int EPI>
-__global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt, int ks, int steps_per_split,
+template <int SRC, int EPI, int WM>
+__global__ void __launch_bounds__(128 * WM, 2) k_gemm_rows(GemvArgs a, int mt, int nt, int ks, int steps_per_split,
                                                       int fused) {
   constexpr bool EXACT_X = SRC == SRC_TAPS;   // inputs already bf16: no lo part
-  constexpr int XT = kGrM * kGrP;             // pieces of one input tile
+  constexpr int TM = WM * kGrM;               // input rows per block
+  constexpr int XT = TM * kGrP;               // pieces of one input tile
   constexpr int ST = (EXACT_X ? 1 : 2) * XT + kGrN * kGrP;
+  constexpr int WR = kGrN / (2 * WM);         // weight rows a wavefront brings
+  constexpr int CP = (EXACT_X ? 2 : 4) + WR / 16;   // copies of a wavefront and step
+  constexpr bool THREE = WM == 4;             // three stages
   __shared__ __attribute__((aligned(16))) gr_u32x4 st0[ST];
   __shared__ __attribute__((aligned(16))) gr_u32x4 st1[ST];
+  __shared__ __attribute__((aligned(16))) gr_u32x4 st2[THREE ? ST : 1];
 
   // ---- this block's tile ------------------------------------------------------------------
   const int tiles = mt * nt, per = (tiles * ks + kGrXcd - 1) / kGrXcd;
   const int id = (int)(blockIdx.x % kGrXcd) * per + (int)(blockIdx.x / kGrXcd);
   if (id >= tiles * ks) return;
   const int split = id / tiles, t = id % tiles;
-  const int g0 = t / (kGrGroup * nt) * kGrGroup, gm = min(kGrGroup, mt - g0);
+  constexpr int GT = kGrGroup / TM;           // row tiles walked together
+  const int g0 = t / (GT * nt) * GT, gm = min(GT, mt - g0);
   const int tg = t - g0 * nt;
-  const int m0 = (g0 + tg % gm) * kGrM, nb = tg / gm;
+  const int m0 = (g0 + tg % gm) * TM, nb = tg / gm;
   const int rows = a.count ? min(*a.count, a.max_rows) : a.max_rows;
   if (m0 >= rows) return;
   const int n0 = nb * (EPI == EPI_SWIGLU ? kGrN / 2 : kGrN);
@@ -79,9 +87,9 @@ __global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt
   const int steps = min(steps_per_split, a.Kd / kGrK - k_beg);
 
   // ---- copies: an instruction fills 16 rows (64 bytes each); a wavefront brings 32 input
-  //      rows and 64 weight rows of every step.  Rows past the end repeat the last one ---------
+  //      rows and WR weight rows of every step.  Rows past the end repeat the last one ---------
   const int cr = lane >> 2;                  // row within an instruction's 16
-  int xo[2], wo[4];
+  int xo[2], wo[WR / 16];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int r = (wave * 2 + i) * 16 + cr;  // row of the tile
@@ -90,12 +98,13 @@ __global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt
     const long src = SRC == SRC_TAPS ? a.tap_row[m] : m;
     xo[i] = (int)(src * ld * 2) + (((lane & 3) ^ ((r >> 1) & 3)) * 16);
   }
-  // gate/up: wavefronts 0 and 2 bring gate rows, 1 and 3 the up rows of the same columns
-  const void* wbase = (EPI == EPI_SWIGLU && (wave & 1)) ? a.w1 : a.w0;
+  // gate/up: the tile's rows are 64 gate rows, the up rows of the same columns, and so on
+  const int w64 = wave * WR / 64;
+  const void* wbase = (EPI == EPI_SWIGLU && (w64 & 1)) ? a.w1 : a.w0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < WR / 16; ++i) {
     const int r = i * 16 + cr;
-    const int n = min(n0 + (EPI == EPI_SWIGLU ? (wave >> 1) * 64 : wave * 64) + r, a.N - 1);
+    const int n = min(n0 + (EPI == EPI_SWIGLU ? (w64 >> 1) * 64 + wave * WR % 64 : wave * WR) + r, a.N - 1);
     wo[i] = (int)((long)n * a.Kd * 2) + (((lane & 3) ^ ((r >> 1) & 3)) * 16);
   }
   auto copy_step = [&](gr_u32x4* st, int k) {
@@ -115,11 +124,12 @@ __global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt
       }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) gr_copy(wbase, st + (ST - kGrN * kGrP) + (wave * 4 + i) * 64, wo[i], col * 2);
+    for (int i = 0; i < WR / 16; ++i)
+      gr_copy(wbase, st + (ST - kGrN * kGrP) + (wave * (WR / 16) + i) * 64, wo[i], col * 2);
   };
 
   // ---- products: wavefront (wm, wn) computes rows 64 wm .., weight rows 128 wn .. -----------
-  const int wm = wave & 1, wn = wave >> 1;
+  const int wm = wave % WM, wn = wave / WM;
   const bool work = m0 + wm * 64 < rows;
   gr_f32x4 acc[8][4];
 #pragma unroll
@@ -150,6 +160,31 @@ __global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt
   // ---- two stages: one fills while the other is multiplied (the barrier waits for the
   //      copies); the stages are arrays of their own, so that reads of one do not wait for
   //      the copies into the other ----------------------------------------------------------
+  if constexpr (THREE) {
+    // Step k: its copies (requested two steps ahead) have arrived when no more than the next
+    // step's are outstanding; past the barrier that holds for every wavefront, and nobody
+    // reads the stage of step k - 1 any more, which takes the copies of step k + 2 (past the
+    // end the last step's again, so that the count stays the same).
+    auto step = [&](gr_u32x4* cur, gr_u32x4* next, int k) {
+      // vmcnt(CP), the other counters at their maximum
+      __builtin_amdgcn_s_waitcnt(0x0f70 | CP);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      copy_step(next, min(k + 2, steps - 1));
+      compute(cur);
+    };
+    copy_step(st0, 0);
+    copy_step(st1, min(1, steps - 1));
+    for (int k = 0; k < steps; k += 3) {
+      step(st0, st2, k);
+      if (k + 1 >= steps) break;
+      step(st1, st0, k + 1);
+      if (k + 2 >= steps) break;
+      step(st2, st1, k + 2);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // no copy into LDS outlives the block
+  } else {
   copy_step(st0, 0);
   __syncthreads();
   for (int k = 0; k < steps; k += 2) {
@@ -160,6 +195,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt
     if (k + 2 < steps) copy_step(st0, k + 2);
     compute(st1);
     __syncthreads();
+  }
   }
 
   // ---- lane holds Y[row 16 m + lane % 16][columns 16 n + 4 (lane / 16) .. + 4) ---------------
@@ -198,10 +234,11 @@ __global__ void __launch_bounds__(256, 2) k_gemm_rows(GemvArgs a, int mt, int nt
   }
 }
 
-// K splits: as many as it takes to give 256 CUs two blocks each, of at least four steps.
-static int gemm_rows_splits(int tiles, int Kd, int& steps_per_split) {
+// K splits: as many as it takes to give 256 CUs two blocks each (of 256 rows: one), of at
+// least four steps.
+static int gemm_rows_splits(int tiles, int blocks, int Kd, int& steps_per_split) {
   const int steps = Kd / kGrK;
-  int ks = std::max(1, std::min(std::min(512 / tiles, steps / 4), kMaxKSplit));
+  int ks = std::max(1, std::min(std::min(blocks / tiles, steps / 4), kMaxKSplit));
   steps_per_split = (steps + ks - 1) / ks;
   return (steps + steps_per_split - 1) / steps_per_split;
 }
@@ -212,21 +249,45 @@ static int gemm_rows_splits(int tiles, int Kd, int& steps_per_split) {
 // rows of equal stride in both input segments; other shapes keep the kernel of gemm_mfma.h.
 bool gemm_rows_supported(SrcKind src, const GemvArgs& a, long input_rows) {
   const long ld = src == SRC_TAPS ? a.ldt : a.ld_xa;
-  return (src == SRC_TAPS || src == SRC_PREP) && a.max_rows > kGrM && a.Kd % kGrK == 0 && a.seg % kGrK == 0 && a.N % 4 == 0 && !a.gather &&
+  return (src == SRC_TAPS || src == SRC_PREP) && a.max_rows > 2 * kGrM && a.Kd % kGrK == 0 && a.seg % kGrK == 0 && a.N % 4 == 0 && !a.gather &&
          (a.seg == 0 || a.ld_xs == a.ld_xa) && input_rows * ld * 2 < (1L << 31) && (long)a.N * a.Kd * 2 < (1L << 31);
 }
 
+// A launch's tiles of 64 WM rows (nper columns each), K splits, and its length: steps per
+// CU, in those of a 128-row block.
+struct GrPlan {
+  int mt, nt, ks, sps;
+  double cost;
+};
+static GrPlan gr_plan(int wm, int rows, int N, int nper, int Kd) {
+  GrPlan p;
+  p.mt = (rows + wm * kGrM - 1) / (wm * kGrM);
+  p.nt = (N + nper - 1) / nper;
+  p.ks = gemm_rows_splits(p.mt * p.nt, wm == 4 ? 256 : 512, Kd, p.sps);
+  const int per_cu = ((p.mt * p.nt * p.ks) + 255) / 256;
+  p.cost = (wm == 4 ? 2 * 0.93 : 1.0) * per_cu * p.sps;
+  return p;
+}
+
+template <int SRC, int EPI, int WM>
+static int launch_tile(const GemvArgs& a, const GrPlan& p, hipStream_t st) {
+  const int grid = (p.mt * p.nt * p.ks + kGrXcd - 1) / kGrXcd * kGrXcd;
+  const int fused = EPI == EPI_SWIGLU && p.ks == 1 && a.act_hi;
+  hipLaunchKernelGGL((k_gemm_rows<SRC, EPI, WM>), dim3(grid), dim3(128 * WM), 0, st, a, p.mt, p.nt, p.ks, p.sps,
+                     fused);
+  return fused ? 0 : p.ks;
+}
+
+// 256-row blocks run a step 7% faster per row (gate/up of 8200 rows, d 2560: 1343 -> 1279 us;
+// taps of 1999 rows, d 1024: 74.5 -> 62.5) where they fill their rounds of 256 CUs as well:
+// 8200 rows make 792 of them for QKV (four rounds, 3.09 full: 20% slower than 1560 of 128
+// rows) and 330 for the taps (598 -> 685 us), 300 rows leave 40% of two empty (a whole
+// prompt 208 -> 225 us).
 template <int SRC, int EPI>
 static int launch_t(const GemvArgs& a, hipStream_t st) {
-  const int mt = (a.max_rows + kGrM - 1) / kGrM;
-  const int per = EPI == EPI_SWIGLU ? kGrN / 2 : kGrN;
-  const int nt = (a.N + per - 1) / per;
-  int sps = 0;
-  const int ks = gemm_rows_splits(mt * nt, a.Kd, sps);
-  const int grid = (mt * nt * ks + kGrXcd - 1) / kGrXcd * kGrXcd;
-  const int fused = EPI == EPI_SWIGLU && ks == 1 && a.act_hi;
-  hipLaunchKernelGGL((k_gemm_rows<SRC, EPI>), dim3(grid), dim3(256), 0, st, a, mt, nt, ks, sps, fused);
-  return fused ? 0 : ks;
+  const int nper = EPI == EPI_SWIGLU ? kGrN / 2 : kGrN;
+  const GrPlan wide = gr_plan(4, a.max_rows, a.N, nper, a.Kd), half = gr_plan(2, a.max_rows, a.N, nper, a.Kd);
+  return wide.cost < half.cost ? launch_tile<SRC, EPI, 4>(a, wide, st) : launch_tile<SRC, EPI, 2>(a, half, st);
 }
 
 int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st) {

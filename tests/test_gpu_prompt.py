@@ -22,6 +22,11 @@ CASES = {
     "group2_hd128": ("p_single128", [(0, 129)]),
     "group2_hd128_turn": ("p_single128", [(1000, 65)]),
     "group4_hd128": ("p_inject", [(0, 70), (511, 17)]),
+    # products by blocks of 256 rows (where they fill the chip's rounds as well as 128 rows
+    # do): taps and down projection, gate/up with K splits, gate/up with SwiGLU in the block
+    "wide_tile_store": ("p_ffn8192_wide_taps", [(0, 700), (0, 700), (5, 649)]),
+    "wide_tile_splits": ("p_ffn4096", [(0, 300), (9, 213)]),
+    "wide_tile_swiglu": ("p_ffn8192", [(0, 300), (9, 213)]),
     "many": ("p_qwen_small", [(b, 4 + b % 3) for b in range(18)]),
     "odd_taps": ("p_odd_taps", [(5, 100), (0, 60)]),
     "wide_taps": ("p_wide_taps", [(0, 65), (3, 2), (64, 63)]),
@@ -48,6 +53,8 @@ def test_prompt_matches_oracle(name, K):
         w = synth.get("p_qwen_small").with_(target_hidden=200)
     elif body == "p_f32_two_layers":
         w = synth.get("p_tiny_f32").with_(n_layers=2)
+    elif body.startswith("p_ffn"):
+        w = synth.get("p_wide_taps" if "taps" in body else "p_qwen_small").with_(d_ffn=int(body[5:9]))
     else:
         w = synth.get(body)
     w = w.with_(name="prompt_" + name, batch=len(seqs), K=max(K, 1), temps=(0.0,), draft_temps=())
