@@ -327,7 +327,9 @@ k_gemv(GemvArgs a, int rows_per_wave) {
   // L2): walked one after another by the same wavefronts, the 16 groups of a 128-token fp32
   // prompt made the launch a chain of as many round trips (QKV of d 256 165 -> 16 us, taps of
   // 1536 columns 75 -> 10 us).
-  for (int r0 = RB * blockIdx.y; r0 < rows; r0 += RB * gridDim.y) {
+  // (Fewer than eight rows to a group: one group, no grid size to fetch.)
+  const int r_beg = RB == 8 ? RB * (int)blockIdx.y : 0, r_step = RB == 8 ? RB * (int)gridDim.y : RB;
+  for (int r0 = r_beg; r0 < rows; r0 += r_step) {
     float xc[RB][XV][VEC];                     // this lane's input values (cached mode)
     float inv_rms[RB];
 #pragma unroll
@@ -590,7 +592,7 @@ inline GemvPlan gemv_plan(int wdtype, EpiKind epi, int rows, int N, int Kd) {
   while (xv < per_lane && xv * 2 * p.rb <= 8) xv *= 2;
   p.xv = xv;
   const int f = epi == EPI_SWIGLU ? 2 : 1;
-  p.groups = std::min((rows + p.rb - 1) / p.rb, kGemvMaxGroups);
+  p.groups = p.rb == 8 ? std::min((rows + 7) / 8, kGemvMaxGroups) : 1;
   const int most = rows > 8 && epi != EPI_LOGITS ? 32 : 8;
   int nw = most == 32 ? 4 : 8;
   while (nw > 1 && nw * xv * p.rb * f > most) nw /= 2;
