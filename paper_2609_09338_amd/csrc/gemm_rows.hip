@@ -64,6 +64,7 @@ __global__ void __launch_bounds__(128 * WM, 2) k_gemm_rows(GemvArgs a, int mt, i
   constexpr int WR = kGrN / (2 * WM);         // weight rows a wavefront brings
   constexpr int CP = (EXACT_X ? 2 : 4) + WR / 16;   // copies of a wavefront and step
   constexpr bool THREE = WM == 4;             // three stages
+  static_assert(CP < 16, "the copies of a step fit the low bits of the wait's vector-memory count");
   __shared__ __attribute__((aligned(16))) gr_u32x4 st0[ST];
   __shared__ __attribute__((aligned(16))) gr_u32x4 st1[ST];
   __shared__ __attribute__((aligned(16))) gr_u32x4 st2[THREE ? ST : 1];
@@ -162,12 +163,14 @@ __global__ void __launch_bounds__(128 * WM, 2) k_gemm_rows(GemvArgs a, int mt, i
   //      the copies into the other ----------------------------------------------------------
   if constexpr (THREE) {
     // Step k: its copies (requested two steps ahead) have arrived when no more than the next
-    // step's are outstanding; past the barrier that holds for every wavefront, and nobody
-    // reads the stage of step k - 1 any more, which takes the copies of step k + 2 (past the
-    // end the last step's again, so that the count stays the same).
+    // step's are outstanding, and this wavefront's reads of the stage of step k - 1 when no
+    // LDS request is; past the barrier both hold for every wavefront, and the copies of step
+    // k + 2 go into the stage of step k - 1 (past the end the last step's again, so that the
+    // count stays the same).  Without the second wait only the instruction order that the
+    // compiler happens to choose would keep a late read apart from the next copy.
     auto step = [&](gr_u32x4* cur, gr_u32x4* next, int k) {
-      // vmcnt(CP), the other counters at their maximum
-      __builtin_amdgcn_s_waitcnt(0x0f70 | CP);
+      // vmcnt(CP) lgkmcnt(0), the export counter at its maximum
+      __builtin_amdgcn_s_waitcnt(0x0070 | CP);
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
