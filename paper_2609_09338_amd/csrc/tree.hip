@@ -13,12 +13,18 @@
 //
 // A wavefront selects a row's k best: the k-th largest of the distinct range maxima in the
 // records bounds them from below (at least k values reach it), so only the logits of the
-// ranges that reach it are read, and those that reach it themselves, hardly more than k,
-// are ranked against each other in one step.  Latency-bound: two dependent loads (records,
-// logits) and about 1 us of arithmetic.  (Rounds of a wavefront arg-best over the 32
-// records and 32 logits of every lane, two rows per wavefront, took 65 us per step for 12
-// sequences of 8 rows, now 20; for one sequence of 4 rows a separate pass over every logit
-// took 7.5 us before a step of 13.4, now one step of 14.6.)
+// ranges that reach it are read, and those that reach it themselves, usually hardly more
+// than k, are ranked against each other in one step.  Where the likely ids are neighbours
+// (one range holds many of them), logits tie, or few ranges hold a mapped row, more than a
+// list of them reaches the bound: then the k ranges of largest max are read, and rounds of
+// the wavefront's best pick the ranges and their logits.  Bound by the latency of dependent
+// steps: records, logits, candidates, d2t and scores, rows, the copy of the conditioning rows.
+// (One sequence of 4 rows: 14.6 us, 20.9 for a separate pass over every logit and a step that
+// merged its blocks; 12 sequences of 8 rows: 20 us, 65 for rounds over 32 records and 32 logits
+// of every lane for two rows per wavefront.  Whole calls with trees, start of that change /
+// likely ids spread / neighbours, copies or few mapped rows: one sequence 757 / 728 / 753-758 us,
+// 12 sequences 2190 / 1645 / 1736-1754; such rows once fell back to one wavefront scanning
+// 151936 logits, 1913-3642 and 6821-7030 us.)
 // A frontier row's attention over its ancestors' and its own keys/values (the tree
 // cache) is one more split of the context attention, added by the split combine.
 #include "common.h"
@@ -44,36 +50,24 @@ OSP_DEV void wave_best(float& v, int& r) {
 // Candidate c is better than candidate e: larger score, lower index on ties.
 OSP_DEV bool cand_better(double s1, int i1, double s2, int i2) { return s1 > s2 || (s1 == s2 && i1 < i2); }
 
-constexpr int kTkRanges = 16;     // record ranges a selection reads (else the row)
-constexpr int kTkList = OSP_WAVE; // logits it ranks (else the row)
+constexpr int kTkRanges = 16;     // record ranges a selection by the bound reads
+constexpr int kTkList = OSP_WAVE; // logits it ranks
 
-// This lane's kMaxTopk best (value, index) pairs, best first: insert one.
-OSP_DEV void top_insert(float (&bv)[kMaxTopk], int (&br)[kMaxTopk], float v, int r) {
-  if (!tk_better(v, r, bv[kMaxTopk - 1], br[kMaxTopk - 1])) return;
+// One round of a wavefront's selection of its best (value, index) pairs: the best over the
+// lanes' N values that are not yet taken (bit q of `gone`: value q), marked as taken by the
+// lane that holds it.  index(q) is this lane's index of value q, 0x7fffffff for none.
+template <int N, typename F>
+OSP_DEV void wave_take_best(const float (&v)[N], F index, unsigned& gone, float& wv, int& wr) {
+  static_assert(N <= 32, "one bit per value");
+  float bv = -INFINITY;
+  int br = 0x7fffffff, bq = 0;
 #pragma unroll
-  for (int i = 0; i < kMaxTopk; ++i) {
-    if (tk_better(v, r, bv[i], br[i])) {
-      const float tv = bv[i];
-      const int tr = br[i];
-      bv[i] = v;
-      br[i] = r;
-      v = tv;
-      r = tr;
-    }
-  }
-}
-
-// The wavefront's best pair over the lanes' lists (wv, wr); the lane holding it drops it.
-OSP_DEV void wave_pop_best(float (&bv)[kMaxTopk], int (&br)[kMaxTopk], float& wv, int& wr) {
-  wv = bv[0];
-  wr = br[0];
+  for (int q = 0; q < N; ++q)
+    if (!((gone >> q) & 1u) && tk_better(v[q], index(q), bv, br)) { bv = v[q]; br = index(q); bq = q; }
+  wv = bv;
+  wr = br;
   wave_best(wv, wr);
-  if (br[0] == wr && bv[0] == wv && wr != 0x7fffffff) {
-#pragma unroll
-    for (int i = 0; i + 1 < kMaxTopk; ++i) { bv[i] = bv[i + 1]; br[i] = br[i + 1]; }
-    bv[kMaxTopk - 1] = -INFINITY;
-    br[kMaxTopk - 1] = 0x7fffffff;
-  }
+  if (br == wr && wr != 0x7fffffff) gone |= 1u << bq;
 }
 
 __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
@@ -171,7 +165,7 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
       }
       __builtin_amdgcn_wave_barrier();
     }
-    if (nl >= K && nl <= kTkList) {
+    if (__builtin_expect(nl >= K && nl <= kTkList, 1)) {
       // lane l holds entry l; its rank is the number of better ones
       const float v = s_lv[j][min(lane, nl - 1)];
       const int e = s_li[j][min(lane, nl - 1)];
@@ -179,16 +173,37 @@ __global__ void __launch_bounds__(kTkThreads) k_tree_step(TreeArgs a) {
       for (int i = 0; i < nl; ++i) rank += tk_better(s_lv[j][i], s_li[j][i], v, e) ? 1 : 0;
       if (rank < K) { s_cv[j][rank] = v; s_cr[j][rank] = e; }
     } else {
-      // ties or masked rows put more ranges or logits at Mk: the whole row
-      float bv[kMaxTopk];
-      int br[kMaxTopk];
+      // The K ranges of largest max, the lower one on ties, hold the K best logits: a logit of
+      // another range has K better ones, the maxima of these (equal maxima lie in lower rows).
+      float mv[kTkRecLane];
 #pragma unroll
-      for (int i = 0; i < kMaxTopk; ++i) { bv[i] = -INFINITY; br[i] = 0x7fffffff; }
-      for (int i = lane; i < a.V; i += OSP_WAVE) top_insert(bv, br, lg[i], i);
+      for (int q = 0; q < kTkRecLane; ++q) mv[q] = lane + q * OSP_WAVE < a.nblk ? rs[q].x : -INFINITY;
+      const auto range_of = [&](int q) { return lane + q * OSP_WAVE < a.nblk ? lane + q * OSP_WAVE : 0x7fffffff; };
+      unsigned gone = 0;
+      for (int t = 0; t < K; ++t) {
+        float wv;
+        int wc;
+        wave_take_best(mv, range_of, gone, wv, wc);
+        if (lane == 0) s_rng[j][t] = wc;
+      }
+      __builtin_amdgcn_wave_barrier();
+      float lv[2 * kMaxTopk];
+      int li[2 * kMaxTopk];
+#pragma unroll
+      for (int i = 0; i < 2 * kMaxTopk; ++i) {
+        const int c = i / 2 < K ? s_rng[j][i / 2] : 0x7fffffff;     // (0x7fffffff: fewer ranges than K)
+        const int at = (i & 1) * OSP_WAVE + lane;
+        const int e = (c < a.nblk ? c : 0) * a.blk_rows + at;
+        lv[i] = lg[min(e, a.V - 1)];
+        li[i] = c < a.nblk && at < a.blk_rows && e < a.V ? e : 0x7fffffff;
+      }
+#pragma unroll
+      for (int i = 0; i < 2 * kMaxTopk; ++i) lv[i] = li[i] < a.V ? lv[i] : -INFINITY;
+      gone = 0;
       for (int t = 0; t < K; ++t) {
         float wv;
         int wr;
-        wave_pop_best(bv, br, wv, wr);
+        wave_take_best(lv, [&](int q) { return li[q]; }, gone, wv, wr);
         if (lane == 0) { s_cv[j][t] = wv; s_cr[j][t] = wr; }
       }
     }

@@ -130,18 +130,20 @@ def tree_flags(res, target_logits, tokens, parents, T, u_acc, u_bonus) -> bool:
     return False
 
 
-def tree_near_tie_keys(tree, tol: float) -> set:
+def tree_near_tie_keys(tree, tol: float, equal: bool = True) -> set:
     """Path keys of the candidates a near tie may move, over every selection the oracle's
     tree growth made: where two neighbouring values that decide the outcome (the cut
     between kept and dropped, and for a node's top-k children also their rank order)
-    are closer than `tol`, every candidate whose value lies within `tol` of that pair."""
+    are closer than `tol`, every candidate whose value lies within `tol` of that pair.
+    equal False: values that are equal by construction are no near tie (their order is
+    given: the lower row, the earlier candidate)."""
     out = set()
     for vals, keys, k, kind in tree.selections:
         pairs = range(min(k, len(vals) - 1)) if kind == "topk" else [k - 1]
         for i in pairs:
             if i + 1 >= len(vals) or not np.isfinite(vals[i + 1]):
                 continue
-            if vals[i] - vals[i + 1] < tol:
+            if vals[i] - vals[i + 1] < tol and (equal or vals[i] != vals[i + 1]):
                 lo, hi = vals[i + 1] - tol, vals[i] + tol
                 out.update(key for v, key in zip(vals, keys) if lo <= v <= hi)
     return out
