@@ -351,15 +351,15 @@ bool attn_rows_supported(int kvdtype, int rows_per_seq, int group) {
   return kvdtype == 1 && rows_per_seq * group > 16;
 }
 
-int attn_rows_tiles(int rows_per_seq, int group) {
+int attn_rows_tiles(int rows, int rows_per_seq, int group) {
   const int nvb = 64 * attn_rows_qt(rows_per_seq * group);
-  return (rows_per_seq * group + nvb - 1) / nvb;
+  return (rows * group + nvb - 1) / nvb;
 }
 
 void launch_attention_rows(const AttnArgs& a, hipStream_t st) {
   const int G = a.nq / a.nkv;
   const int qt = attn_rows_qt(a.rows_per_seq * G);
-  const int n_tiles = attn_rows_tiles(a.rows_per_seq, G);
+  const int n_tiles = attn_rows_tiles(a.rows_per_seq, a.rows_per_seq, G);
   const dim3 grid(a.nkv, n_tiles * a.B, a.n_split);
   if (a.hd == 128) {
     if (qt == 2) hipLaunchKernelGGL((k_attn_rows<128, 2>), grid, dim3(256), 0, st, a, n_tiles);

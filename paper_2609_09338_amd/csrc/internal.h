@@ -326,10 +326,10 @@ struct AttnArgs {
 void launch_attention(int kvdtype, const AttnArgs& a, hipStream_t st);
 // The same for passes of many query vectors per sequence (bf16 caches; a.q_prep set, a.cu
 // groups the rows, whose positions ascend within a sequence): blocks of query vectors, each
-// walking its pages once.  attn_rows_tiles: blocks per kv head and split of one sequence of
-// `rows_per_seq` rows whose kv heads serve `group` query heads.
+// walking its pages once.  attn_rows_tiles: blocks per kv head and split of `rows` rows in a
+// pass of at most `rows_per_seq` rows per sequence, whose kv heads serve `group` query heads.
 bool attn_rows_supported(int kvdtype, int rows_per_seq, int group);
-int attn_rows_tiles(int rows_per_seq, int group);
+int attn_rows_tiles(int rows, int rows_per_seq, int group);
 void launch_attention_rows(const AttnArgs& a, hipStream_t st);
 // The merge of its splits into o_hi / o_lo (not for tree passes).
 void launch_attn_join(const AttnArgs& a, hipStream_t st);

@@ -369,6 +369,8 @@ constexpr long kKvStreamBytes = 160L << 20;   // pages of a pass over every laye
 struct SplitPlan {
   int n_split, split_len;
   bool kv_stream;   // the context's pages over every layer outsize the last-level cache
+  long ctx_total;   // positions of all sequences
+  long tile_ctx;    // the ingest's blocks of query vectors per kv head, times their contexts
 };
 SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int max_split = kMaxSplit,
                       int min_len = 64) {
@@ -382,6 +384,8 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
   len = std::min<long>(len, kMaxSplitLen);
   len = (len + 15) / 16 * 16;
   SplitPlan p;
+  p.ctx_total = ctx_total;
+  p.tile_ctx = 0;
   p.split_len = (int)len;
   p.n_split = (int)std::max<long>(1, (ctx_max + len - 1) / len);
   // Pages that cannot stay in the 256 MB last-level cache from one pass to the next are
@@ -399,19 +403,30 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
 // splits: a 1999-token prompt (256 tiles) 480 / 473 / 461 / 468 / 465 / 470 us, two turns of
 // 770 tokens over 7000 positions (104) 754 / 643 / 588 / 601 / 580 / 585, four prompts of
 // 3600 tokens (450) 649 / 680 / 676 / 684 / 687 / 699.
+// A long context among short ones is cut further: no block walks more than twice the
+// positions that an even deal of the pass's work would give it.  (Equal contexts never reach
+// that bound.)  Ingests of 16 rows for 64 sequences, one over 131000 positions and 63 over 512,
+// with their first drafts and verification 3913 -> 1081 us (chains of two, d 2560: 6676 -> 3756);
+// with a longest context of 32768 3718 -> 3036, eight prompts beside one such turn 1680 -> 1429.
 constexpr long kRowSplitLen = 128;
 SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, int rows_per_seq, int rows,
-                          int max_split) {
+                          bool tree) {
   const osprey_config& c = h->cfg;
   const int group = c.n_q_heads / c.n_kv_heads;
   const long ctx = (long)sp.n_split * sp.split_len;   // at least the longest context
   // a batch's tiles: the longest sequence's, and no more than its rows fill
-  const int per_seq = attn_rows_tiles(rows_per_seq, group);
-  const long tiles = std::min<long>((long)B * per_seq, (long)attn_rows_tiles(rows, group) + B);
+  const int per_seq = attn_rows_tiles(rows_per_seq, rows_per_seq, group);
+  const long tiles = std::min<long>((long)B * per_seq, (long)attn_rows_tiles(rows, rows_per_seq, group) + B);
+  const int max_split = tree ? kMaxSplit - 1 : kMaxSplit;   // (a tree row's own branch is one more)
   long n = 7L * h->n_cu / (2 * tiles * c.n_kv_heads);
   n = std::max<long>(1, std::min<long>(std::min<long>(n, max_split), ctx / kRowSplitLen));
   SplitPlan p = sp;
-  long len = ((ctx + n - 1) / n + 63) / 64 * 64;
+  long len = (ctx + n - 1) / n;
+  const long work = tree ? sp.ctx_total * per_seq : sp.tile_ctx;
+  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu);
+  len = std::min(len, std::max(2 * even, kRowSplitLen));
+  len = std::max(len, (ctx + max_split - 1) / max_split);
+  len = (len + 63) / 64 * 64;
   p.split_len = (int)len;
   p.n_split = (int)((ctx + len - 1) / len);
   return p;
@@ -827,7 +842,7 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
     // block of vectors instead of once per 16 vectors (attention_rows.hip).
     const bool by_rows = a.q_prep && attn_rows_supported(c.dtype, rows_per_seq, nq / nkv);
     if (by_rows) {
-      const SplitPlan rp = plan_row_splits(h, sp, B, rows_per_seq, rows.max_rows, tree ? kMaxSplit - 1 : kMaxSplit);
+      const SplitPlan rp = plan_row_splits(h, sp, B, rows_per_seq, rows.max_rows, tree != nullptr);
       a.n_split = rp.n_split;
       a.split_len = rp.split_len;
       a.direct = rp.n_split == 1 && !tree;
@@ -1342,6 +1357,13 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
   if (split.n_split > max_split)
     return fail(OSPREY_E_UNSUPPORTED, "a context of %ld positions needs %d splits (at most %d)", ctx_max,
                 split.n_split, max_split);
+  for (int b = 0; b < B; ++b) {
+    const SlotHost& s = h->slots[a->slots[b]];
+    const int n = pending ? s.drafted_k + 1 : a->n_new[b];
+    const long need = std::max(s.len_max + n + extra, h->ctx_plan);
+    const int tail = block_mask >= 0 ? extra : 0;
+    split.tile_ctx += need * attn_rows_tiles(n + tail, max_new + tail, c.n_q_heads / c.n_kv_heads);
+  }
   tt = h->t_begin(3);
   // ---- row layout of the ingest ---------------------------------------------------------
   SetupArgs sa{};

@@ -1,0 +1,109 @@
+"""Batches of many sequences whose ingest attends by blocks of query vectors: contexts that
+fill a block's walk past 4096 positions (its page-table entries are fetched 64 steps at a
+time), and one long context among short ones."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import harness as OH
+
+pytestmark = pytest.mark.gpu
+
+# 8 kv heads of 2 query heads: 64 sequences fill the chip without splitting their contexts
+BODY = synth.get("p_qwen_small").with_(n_q_heads=16, n_kv_heads=8, batch=64, K=1, temps=(0.0,), draft_temps=())
+
+
+def _drafter(w, weights, d2t, ctx, rows, max_k=1):
+    """A drafter over shuffled pages whose contexts hold random keys and values."""
+    from paper_2609_09338_amd import _lib as L
+    from paper_2609_09338_amd import workload as WL
+    from paper_2609_09338_amd.binding import Drafter, make_config
+    B = len(ctx)
+    need = [synth.blocks_needed(w, c + n + 3 * max_k) for c, n in zip(ctx, rows)]
+    blocks = synth.block_ids(w, need)
+    cfg = make_config(n_layers=w.n_layers, d_model=w.d_model, n_q_heads=w.n_q_heads, n_kv_heads=w.n_kv_heads,
+                      head_dim=w.head_dim, d_ffn=w.d_ffn, vocab_draft=w.vocab_draft, vocab_target=w.vocab_target,
+                      target_hidden=w.target_hidden, dtype=L.OSPREY_BF16, qk_norm=w.qk_norm, max_batch=B,
+                      max_k=max_k, max_seq_len=16 * max(need), kv_num_blocks=sum(need),
+                      max_new_rows=max(sum(rows), B * (max_k + 1)))
+    dr = Drafter(cfg, {k: WL.to_dev(v, w, "cuda:0") for k, v in weights.items()}, torch.from_numpy(d2t).to("cuda:0"))
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(7)
+    kv = {}
+    dr.kv.fill_(0xFF)          # unwritten cache memory is NaN: nothing may read it
+    for b in range(B):
+        dr.seq_reset(b, blocks[b])
+        if ctx[b]:
+            kv[b] = [torch.randn((w.n_layers, ctx[b], w.n_kv_heads, w.head_dim), generator=g, device="cuda:0").bfloat16()
+                     for _ in "kv"]
+            dr.kv_append(b, *kv[b])
+    return dr, kv
+
+
+@pytest.mark.parametrize("name,ctx,rows,check", [
+    # rows on both sides of position 4096, where the second fetch of page-table entries begins
+    ("past_4096", [4075 + b % 24 for b in range(64)], [9 + b % 8 for b in range(64)], [0, 13, 22, 23]),
+    ("one_long", [3000 if b == 31 else 5 + b for b in range(64)], [9 + b % 8 for b in range(64)], [0, 31, 63])])
+def test_batches_over_long_contexts_match_oracle(name, ctx, rows, check):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import workload as WL
+    w = BODY
+    weights, d2t = synth.make_weights(w), synth.make_d2t(w)
+    dr, kv = _drafter(w, weights, d2t, ctx, rows)
+    toks = [synth.prompt_tokens(w, b, n) for b, n in enumerate(rows)]
+    taps = [synth.taps(w, 0, b, n) for b, n in enumerate(rows)]
+    logits = torch.empty((len(rows), 1, w.vocab_draft), device="cuda:0")
+    print(f"[mixed batch] {name}", flush=True)
+    B = len(rows)
+    dr.draft_step(list(range(B)), 1, WL.to_dev(np.concatenate(taps), w, "cuda:0"), torch.zeros(B, device="cuda:0"),
+                  n_new=rows, new_tokens=torch.from_numpy(np.concatenate(toks)).to("cuda:0"),
+                  draft_tokens=torch.empty((B, 1), dtype=torch.int32, device="cuda:0"), draft_logits=logits)
+    torch.cuda.synchronize()
+    assert dr.device_errors() == 0
+    o = OH.build_drafter(w, weights, d2t)
+    for b in check:
+        seq = OH.Sequence(w, ctx[b] + rows[b] + 1)
+        seq.k[:, :ctx[b]], seq.v[:, :ctx[b]] = (t.double().cpu().numpy() for t in kv[b])
+        seq.length = ctx[b]
+        _, want, _, _ = o.draft(seq, toks[b], taps[b].astype(np.float64), 1, 0.0, np.zeros(1))
+        err = np.max(np.abs(logits[b].cpu().numpy() - want))
+        print(f"[mixed batch] {name} sequence {b}: max |dlogit| {err:.1e}", flush=True)
+        # (a quarter of what the parity tests allow; a wrong page past position 4096 moves the
+        # logits by 0.04 to 0.08)
+        assert err < 5e-3
+
+
+def test_one_long_context_does_not_hold_up_the_batch():
+    """One context of 130000 positions among 63 of 500: the ingest costs about what it costs
+    without the long one and what the long one costs alone, not one block's walk over it (3.1 ms
+    a layer).  Measured 552 us against 221 and 187."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    w = BODY.with_(head_dim=128)
+    weights, d2t = synth.make_weights(w), synth.make_d2t(w)
+
+    def us(ctx):
+        rows = [16] * len(ctx)
+        dr, _ = _drafter(w, weights, d2t, ctx, rows)
+        toks = torch.zeros(sum(rows), dtype=torch.int32, device="cuda:0")
+        taps = torch.ones((sum(rows), w.tap_width), dtype=torch.bfloat16, device="cuda:0")
+        temp, best = torch.zeros(len(ctx), device="cuda:0"), 1e9
+        for _ in range(6):
+            for b, c in enumerate(ctx):
+                dr.seq_truncate(b, c)
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            torch.cuda.synchronize()
+            e[0].record()
+            dr.draft_step(list(range(len(ctx))), 0, taps, temp, n_new=rows, new_tokens=toks)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) * 1e3)
+        assert dr.device_errors() == 0
+        return best
+
+    print("[mixed batch] one long context", flush=True)
+    both, short, long = us([500] * 40 + [130000] + [500] * 23), us([500] * 63), us([130000])
+    print(f"[mixed batch] {both:.0f} us; without the long one {short:.0f}, the long one alone {long:.0f}", flush=True)
+    assert both < 2 * (short + long)
