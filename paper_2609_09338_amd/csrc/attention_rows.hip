@@ -21,8 +21,8 @@
 //     and no register moves per value fragment.
 // The matrix cores bound it (four products per score and value, hi and lo): registers
 // hold two wavefronts per SIMD, so one's softmax overlaps another's products.
-// Blocks are (kv head, row tile and sequence, context split): heads go to the XCDs in
-// turn, so each L2 holds the pages of the heads it serves, and the tiles of the longest
+// Blocks are kv head, sequence, row tile (one grid dimension, the head innermost) and
+// context split: heads go to the XCDs in turn, so each L2 holds the pages of the heads it serves, and the tiles of the longest
 // contexts start first.  With one split the output is written directly (hi / lo pairs);
 // a pass of too few tiles to fill the chip splits its context, and the merge kernel or
 // the O projection joins the partials.
@@ -35,6 +35,8 @@
 #include "common.h"
 #include "internal.h"
 
+#include <algorithm>
+
 namespace osp {
 
 typedef __bf16 ar_bf16x8 __attribute__((ext_vector_type(8)));
@@ -45,7 +47,7 @@ constexpr int kArTok = 64;   // tokens per step: a page per wavefront
 constexpr int kArPage = 16;
 
 template <int HD, int QT>
-__global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles) {
+__global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles, int tiles_x) {
   constexpr int KC = HD / 32;             // 32-wide head-dim chunks of K Q^T
   constexpr int NT = HD / 16;             // 16-dim output tiles
   constexpr int KROW = HD / 8;            // 16-byte pieces of a key row
@@ -55,8 +57,9 @@ __global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles) {
   __shared__ __attribute__((aligned(16))) ar_u32x4 sk[2][kArTok * KROW];
   __shared__ __attribute__((aligned(16))) ar_u32x4 sv[2][kArTok * KROW];
 
-  const int g = blockIdx.x;
-  const int b = blockIdx.y % a.B, tile = n_tiles - 1 - (int)blockIdx.y / a.B;
+  const int g = blockIdx.x % a.nkv, bt_id = blockIdx.x / a.nkv;
+  const int b = bt_id % a.B, tile = n_tiles - 1 - (bt_id / a.B + (int)blockIdx.y * tiles_x);
+  if (tile < 0) return;
   const int sp = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -360,13 +363,16 @@ void launch_attention_rows(const AttnArgs& a, hipStream_t st) {
   const int G = a.nq / a.nkv;
   const int qt = attn_rows_qt(a.rows_per_seq * G);
   const int n_tiles = attn_rows_tiles(a.rows_per_seq, a.rows_per_seq, G);
-  const dim3 grid(a.nkv, n_tiles * a.B, a.n_split);
+  // Grid y and z end at 65536, which (row tile, sequence) pairs can pass (257 tiles of 256
+  // sequences), and x at 2^32 threads: x takes up to 2^20 blocks, then y further tiles.
+  const int tiles_x = std::min(n_tiles, std::max(1, (1 << 20) / (a.nkv * a.B)));
+  const dim3 grid(a.nkv * a.B * tiles_x, (n_tiles + tiles_x - 1) / tiles_x, a.n_split);
   if (a.hd == 128) {
-    if (qt == 2) hipLaunchKernelGGL((k_attn_rows<128, 2>), grid, dim3(256), 0, st, a, n_tiles);
-    else hipLaunchKernelGGL((k_attn_rows<128, 1>), grid, dim3(256), 0, st, a, n_tiles);
+    if (qt == 2) hipLaunchKernelGGL((k_attn_rows<128, 2>), grid, dim3(256), 0, st, a, n_tiles, tiles_x);
+    else hipLaunchKernelGGL((k_attn_rows<128, 1>), grid, dim3(256), 0, st, a, n_tiles, tiles_x);
   } else {
-    if (qt == 2) hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, dim3(256), 0, st, a, n_tiles);
-    else hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, dim3(256), 0, st, a, n_tiles);
+    if (qt == 2) hipLaunchKernelGGL((k_attn_rows<64, 2>), grid, dim3(256), 0, st, a, n_tiles, tiles_x);
+    else hipLaunchKernelGGL((k_attn_rows<64, 1>), grid, dim3(256), 0, st, a, n_tiles, tiles_x);
   }
 }
 

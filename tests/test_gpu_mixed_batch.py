@@ -75,6 +75,42 @@ def test_batches_over_long_contexts_match_oracle(name, ctx, rows, check):
         assert err < 5e-3
 
 
+def test_prompt_beside_255_sequences_matches_oracle():
+    """A 2100-row prompt in a batch of 256: 263 blocks of 128 query vectors per sequence, more
+    (block, sequence) pairs than a grid's y dimension takes."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import workload as WL
+    w = synth.get("p_single64").with_(d_model=64, n_q_heads=16, n_kv_heads=1, d_ffn=64, vocab_draft=997, vocab_target=997,
+                                      target_hidden=8, batch=256, K=1, temps=(0.0,), draft_temps=())
+    weights, d2t = synth.make_weights(w), synth.make_d2t(w)
+    B, at = 256, 200
+    rows = [2100 if b == at else 1 + b % 2 for b in range(B)]
+    dr, _ = _drafter(w, weights, d2t, [0] * B, rows)
+    toks = [synth.prompt_tokens(w, b, n) for b, n in enumerate(rows)]
+    taps = [synth.taps(w, 0, b, n) for b, n in enumerate(rows)]
+    logits = torch.empty((B, 1, w.vocab_draft), device="cuda:0")
+    print("[mixed batch] a prompt beside 255 sequences", flush=True)
+    dr.draft_step(list(range(B)), 1, WL.to_dev(np.concatenate(taps), w, "cuda:0"), torch.zeros(B, device="cuda:0"),
+                  n_new=rows, new_tokens=torch.from_numpy(np.concatenate(toks)).to("cuda:0"),
+                  draft_tokens=torch.empty((B, 1), dtype=torch.int32, device="cuda:0"), draft_logits=logits)
+    torch.cuda.synchronize()
+    assert dr.device_errors() == 0
+    o = OH.build_drafter(w, weights, d2t)
+    kv = dr.kv.view(torch.bfloat16).float().cpu().numpy().reshape(-1, w.n_layers, 2, 1, 16 * w.head_dim)
+    blocks = synth.block_ids(w, [synth.blocks_needed(w, n + 3) for n in rows])
+    for b in (0, 1, at, 255):
+        seq = OH.Sequence(w, rows[b] + 1)
+        _, want, _, _ = o.draft(seq, toks[b], taps[b].astype(np.float64), 1, 0.0, np.zeros(1))
+        err = np.max(np.abs(logits[b].cpu().numpy() - want))
+        # the second layer's keys: every row's first-layer attention reaches them
+        got = kv[blocks[b], 1, 0].reshape(-1, w.head_dim)[:rows[b]]
+        k = seq.k[1, :rows[b], 0]
+        off = np.max(np.abs(got - k) - 2.0 ** -8 * np.abs(k))
+        print(f"[mixed batch] sequence {b}: max |dlogit| {err:.1e}, keys beyond a rounding {off:.1e}", flush=True)
+        assert err < 2e-2 and off < 2e-2
+
+
 def test_one_long_context_does_not_hold_up_the_batch():
     """One context of 130000 positions among 63 of 500: the ingest costs about what it costs
     without the long one and what the long one costs alone, not one block's walk over it (3.1 ms
