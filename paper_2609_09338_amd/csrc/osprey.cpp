@@ -12,6 +12,7 @@
 
 #include "../../include/osprey.h"
 #include "internal.h"
+#include "narrow.h"
 
 #define OSPREY_API extern "C" __attribute__((visibility("default")))
 
@@ -482,15 +483,11 @@ void append_args(osprey_handle* h, AttnArgs& a, const RowMeta& rows, const ospre
   a.err = W.err;
 }
 
-// Passes of the vector body narrow their last layer (run_body's `keep`) from this many
-// rows on: it computes eight rows at a time.
-constexpr int kNarrowRows = 16;
-
 // One forward pass of the body over `rows`; `s` holds the conditioning rows.  `pick`
 // (a single sequence's draft step): layer 0 draws the step's token itself.
 // `keep`: the rows whose output is used: -1 every row, 0 none (an ingest without drafts:
 // the last layer ends with its keys and values), B each sequence's last row (W.last_row):
-// a long ingest then appends the last layer's keys and values for every row and runs its
+// where it pays (narrow.h) an ingest then appends the last layer's keys and values for every row and runs its
 // attention, FFN and norm on B rows, left in rows 0 .. B - 1 (no later step reads another
 // row).  Whole calls: a 1999-token prompt 742 -> 497 us, four prompts of 8200 tokens (d 2560)
 // 10.6 -> 7.1 ms, two turns of 770 tokens 864 -> 625 us, a 128-token prompt and two fp32
@@ -502,7 +499,7 @@ bool run_body(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const fl
   const Ws& W = h->W;
   const int d = c.d_model, hd = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads;
   const int qkv_w = h->D.qkv_rows;
-  const bool narrow = keep == 0 || (keep > 0 && rows.max_rows >= kNarrowRows && rows.max_rows > keep);
+  const bool narrow = keep == 0 || (keep > 0 && narrow_pays(c, rows.max_rows, keep));
   for (int l = 0; l < c.n_layers; ++l) {
     const osprey_layer_weights& L = h->layers[l];
     // expanded QKV over [s ; RMSNorm(x)] (Eq. 2-3)
@@ -725,8 +722,7 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
   gb.count = rows.count;
   gb.xa_hi = W.xa_hi;
   gb.xa_lo = W.xa_lo;
-  // (up to kLmMaxRows rows a layer costs its launches, not its rows: nothing to gain)
-  const bool narrow = keep == 0 || (keep > 0 && rows.max_rows > kLmMaxRows);
+  const bool narrow = keep == 0 || (keep > 0 && narrow_pays(c, rows.max_rows, keep));
   for (int l = 0; l < c.n_layers; ++l) {
     const osprey_layer_weights& L = h->layers[l];
     // The last layer's other rows only add their keys and values to the cache.

@@ -28,6 +28,11 @@ CASES = {
     "wide_tile_splits": ("p_ffn4096", [(0, 300), (9, 213)]),
     "wide_tile_swiglu": ("p_ffn8192", [(0, 300), (9, 213)]),
     "many": ("p_qwen_small", [(b, 4 + b % 3) for b in range(18)]),
+    # more than 64 sequences: nothing to narrow (a row each), too little, and kept rows that
+    # take more than one streaming pass
+    "one_each_b70": ("p_qwen_small", [(b % 5, 1) for b in range(70)]),
+    "two_each_b66": ("p_qwen_small", [(b % 5, 2) for b in range(66)]),
+    "four_each_b66": ("p_qwen_small", [(b % 5, 4) for b in range(66)]),
     "odd_taps": ("p_odd_taps", [(5, 100), (0, 60)]),
     "wide_taps": ("p_wide_taps", [(0, 65), (3, 2), (64, 63)]),
     "f32": ("p_tiny_f32", [(0, 65)]),
