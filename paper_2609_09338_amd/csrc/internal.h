@@ -212,7 +212,8 @@ void launch_pack_head(const void* w, int N, int Kd, void* packed, hipStream_t st
 // src SRC_PREP (pairs; [xs ; xa] when seg > 0), SRC_TAPS, or SRC_SWIGLU (the down
 // projection forms silu(gate) * up from the gate/up partials itself); with w1 set, the up
 // matrix supplies rows [N, 2N).  Writes K-split partial sums to
-// split_buf[split][max_rows][N or 2N]; returns the number of splits.
+// split_buf[split][max_rows][N or 2N]; returns the number of splits, or 0 for more rows than
+// that (nothing launched).
 int launch_skinny(SrcKind src, const GemvArgs& a, hipStream_t st);
 int skinny_splits(int rows, int Kd);
 

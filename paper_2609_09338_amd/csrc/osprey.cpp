@@ -352,8 +352,16 @@ int check_slot(osprey_handle* h, int slot) {
   return OSPREY_OK;
 }
 
+// A kernel of the current call was refused (launched nothing): the call fails.  Per host
+// thread, as the error message; hip_last reports and clears it.
+thread_local bool g_refused = false;
+
 int hip_last() {
   hipError_t e = hipGetLastError();
+  if (g_refused) {
+    g_refused = false;
+    return fail(OSPREY_E_UNSUPPORTED, "a streaming product takes at most %d rows (%d prepared)", kLmMaxRows, kSkMaxRows);
+  }
   if (e != hipSuccess) return fail(OSPREY_E_DEVICE, "kernel launch: %s", hipGetErrorString(e));
   return ok();
 }
@@ -670,11 +678,19 @@ struct TreePass {
   const int32_t* bslot;     // [B] each sequence's cache slot (its committed context)
 };
 
+// launch_skinny; a refusal fails the call (the kernels that follow find one split to read).
+int stream_product(SrcKind src, const GemvArgs& g, hipStream_t st) {
+  const int ks = launch_skinny(src, g, st);
+  if (ks > 0) return ks;
+  g_refused = true;
+  return 1;
+}
+
 // A product of a pass of more than kLmMaxRows rows: up to kSkMaxRows prepared rows stream the
 // weights once (width 1024, 96 rows: 10.5 us a product against 12.1 of gemm_mfma.h's two
 // 64-row blocks), larger passes take the tiled products.
 int gemm_large(SrcKind src, EpiKind epi, const GemvArgs& g, long input_rows, hipStream_t st) {
-  if (src == SRC_PREP && g.max_rows <= kSkMaxRows) return launch_skinny(src, g, st);
+  if (src == SRC_PREP && g.max_rows <= kSkMaxRows) return stream_product(src, g, st);
   return gemm_rows_supported(src, g, input_rows) ? launch_gemm_rows(src, epi, g, st) : launch_gemm(src, epi, g, st);
 }
 
@@ -690,7 +706,7 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
   float* part = skinny ? W.split_s : W.split;
   auto gemm = [&](SrcKind src, EpiKind epi, GemvArgs& g) -> int {
     g.split_buf = part;
-    return skinny ? launch_skinny(src, g, h->stream) : gemm_large(src, epi, g, rows.max_rows, h->stream);
+    return skinny ? stream_product(src, g, h->stream) : gemm_large(src, epi, g, rows.max_rows, h->stream);
   };
   const int d = c.d_model, hd = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads, F = c.d_ffn;
   const int qkv_w = h->D.qkv_rows;
@@ -904,7 +920,7 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
       gd.ld_in = 2 * F;
       gd.split_buf = W.split_s2;
       rd.part = W.split_s2;
-      rd.ks = launch_skinny(SRC_SWIGLU, gd, h->stream);
+      rd.ks = stream_product(SRC_SWIGLU, gd, h->stream);
     } else {
       if (rs.ks > 0) {
         launch_rows_swiglu(rs, h->stream);
@@ -1300,6 +1316,7 @@ namespace {
 int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, SplitPlan& split,
                 bool& pending, int& tt, int max_split, int block_mask, int keep, bool& narrow) {
   int rc;
+  g_refused = false;
   const osprey_config& c = h->cfg;
   const int B = a->batch;
   if (!a->slots || !a->taps || !a->temperature) return fail(OSPREY_E_INVALID, "slots, taps and temperature must be non-NULL");
@@ -1422,7 +1439,7 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
     int ks_taps;
     if (rows <= kLmMaxRows) {
       gt.split_buf = W.split_s;
-      ks_taps = launch_skinny(SRC_TAPS, gt, h->stream);
+      ks_taps = stream_product(SRC_TAPS, gt, h->stream);
     } else {
       // (tap rows: b taps_stride + j, or packed)
       const long tap_rows = a->taps_stride > 0 ? (long)B * a->taps_stride : rows;

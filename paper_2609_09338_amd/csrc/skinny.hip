@@ -689,8 +689,9 @@ bool lm_head_norm_in_supported(int rows, int Kd) { return rows == 1 && Kd <= 8 *
 
 bool launch_lm_head(const GemvArgs& a, const LmPlan& p, bool norm_in, hipStream_t st) {
   // the fp32 input is normalised in the head for one row only (batch 1), of at most
-  // 8 x kSkThreads columns; anything else is refused (nothing launched)
-  if (norm_in && !lm_head_norm_in_supported(a.max_rows, a.Kd)) return false;
+  // 8 x kSkThreads columns, prepared rows up to kSkMaxRows; anything else is refused (nothing
+  // launched)
+  if (a.max_rows > kSkMaxRows || (norm_in && !lm_head_norm_in_supported(a.max_rows, a.Kd))) return false;
   if (norm_in) sk_launch<SK_NORM, SK_LOGITS>(1, dim3(p.grid), a, p.T, 0, st);
   else sk_launch<SK_PREP, SK_LOGITS>(sk_mt(a.max_rows), dim3(p.grid), a, p.T, 0, st);
   return true;
@@ -743,6 +744,8 @@ int skinny_splits(int rows, int Kd) {
 }
 
 int launch_skinny(SrcKind src, const GemvArgs& a, hipStream_t st) {
+  // (only prepared rows have an instance of six row tiles)
+  if (a.max_rows > (src == SRC_PREP ? kSkMaxRows : kLmMaxRows)) return 0;
   const int mt = sk_mt(a.max_rows);
   const int NR = a.w1 ? 2 * a.N : a.N;
   // (attention outputs: K ranges of one unit, so that a block's range holds at most 4
