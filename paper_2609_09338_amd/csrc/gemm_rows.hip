@@ -248,12 +248,16 @@ static int gemm_rows_splits(int tiles, int blocks, int Kd, int& steps_per_split)
 
 // Passes of more than 128 rows (below, one 128-row tile leaves a wavefront pair idle and
 // too few blocks: at 96 rows of width 1024 the products took 11.7-13.2 us against
-// 11.3-12.1); whole 32-column steps, inputs and weights within the 2 GB a buffer offset reaches, and
-// rows of equal stride in both input segments; other shapes keep the kernel of gemm_mfma.h.
+// 11.3-12.1); whole 32-column steps, inputs and weights within the 2 GB a buffer offset reaches, on
+// 16-byte boundaries (the copies into LDS move 16 bytes; rows are whole pieces, so the
+// caller's taps and weights decide), and rows of equal stride in both input segments; other
+// shapes keep the kernel of gemm_mfma.h.
 bool gemm_rows_supported(SrcKind src, const GemvArgs& a, long input_rows) {
   const long ld = src == SRC_TAPS ? a.ldt : a.ld_xa;
+  const auto at16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   return (src == SRC_TAPS || src == SRC_PREP) && a.max_rows > 2 * kGrM && a.Kd % kGrK == 0 && a.seg % kGrK == 0 && a.N % 4 == 0 && !a.gather &&
-         (a.seg == 0 || a.ld_xs == a.ld_xa) && input_rows * ld * 2 < (1L << 31) && (long)a.N * a.Kd * 2 < (1L << 31);
+         (a.seg == 0 || a.ld_xs == a.ld_xa) && input_rows * ld * 2 < (1L << 31) && (long)a.N * a.Kd * 2 < (1L << 31) &&
+         at16(a.w0) && at16(a.w1) && (src != SRC_TAPS || at16(a.taps));
 }
 
 // A launch's tiles of 64 WM rows (nper columns each), K splits, and its length: steps per
