@@ -391,8 +391,10 @@ int osprey_verify_tree(osprey_handle* h, const osprey_verify_tree_args* a);
  * K and slots in both argument sets, taps_stride >= K + 1, kernel timing off, and a
  * stream other than the null stream (osprey_set_stream).  Attention is planned for
  * contexts up to max_context positions (<= max_seq_len): every launch must keep each
- * slot's committed length + pending tokens + K - 1 within it.  Capturing changes no
- * state and enqueues nothing; errors are those of the two calls.
+ * slot's committed length + pending tokens + K - 1 within it.  The ingest is planned for
+ * min(taps_stride, max_k + 1) pending tokens per slot (K + 1, where the workspace holds no
+ * more rows), whatever the slots hold at capture; a launch that could find more is refused.
+ * Capturing changes no state and enqueues nothing; errors are those of the two calls.
  *
  * osprey_graph_launch enqueues one iteration on the handle's stream: the same
  * checks as the two calls (every slot VERIFIED, capacity within its pages and

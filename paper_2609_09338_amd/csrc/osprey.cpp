@@ -310,6 +310,7 @@ struct osprey_handle {
   // graph capture: attention splits are planned for contexts up to this bound (0: the
   // call's own contexts), so that replays of a captured iteration stay covered
   long ctx_plan = 0;
+  int pend_plan = 0;    // likewise its pending rows per sequence (0: the slots' own bounds)
   // timing: bit f of `timing` enables event timing of family f
   int timing = 0;
   std::vector<TimerRec> timers;
@@ -1307,6 +1308,13 @@ OSPREY_API int osprey_seq_length(osprey_handle* h, int32_t slot, int32_t* length
 
 namespace {
 
+// New rows of sequence b that a call is planned for: the given ones, or the bound of the
+// pending ones (in a capture: of any launch's, not of what the slot holds then).
+int planned_rows(const osprey_handle* h, const osprey_step_args* a, int b) {
+  if (a->n_new) return a->n_new[b];
+  return h->pend_plan > 0 ? h->pend_plan : h->slots[a->slots[b]].drafted_k + 1;
+}
+
 // Validation, row layout and ingest of a draft call: the new rows of every sequence
 // through the tap projection (Eq. 1) and the body.  K: the chain's drafts (the setup
 // kernel's autoregressive positions); extra: positions past the ingest the call will
@@ -1347,6 +1355,8 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
     const long need = s.len_max + n + extra;
     if (need > (long)s.nblocks * c.kv_block || need > c.max_seq_len)
       return fail(OSPREY_E_CAPACITY, "slot %d: up to %ld positions exceed its %d pages / max_seq_len", slot, need, s.nblocks);
+    // (a captured pass is planned for the most that a later launch may find pending)
+    n = planned_rows(h, a, b);
     rows += n + (block_mask >= 0 ? extra : 0);
     max_new = std::max(max_new, n);
     ctx_max = std::max(ctx_max, need);
@@ -1371,9 +1381,8 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
     return fail(OSPREY_E_UNSUPPORTED, "a context of %ld positions needs %d splits (at most %d)", ctx_max,
                 split.n_split, max_split);
   for (int b = 0; b < B; ++b) {
-    const SlotHost& s = h->slots[a->slots[b]];
-    const int n = pending ? s.drafted_k + 1 : a->n_new[b];
-    const long need = std::max(s.len_max + n + extra, h->ctx_plan);
+    const int n = planned_rows(h, a, b);
+    const long need = std::max(h->slots[a->slots[b]].len_max + n + extra, h->ctx_plan);
     const int tail = block_mask >= 0 ? extra : 0;
     split.tile_ctx += need * attn_rows_tiles(n + tail, max_new + tail, c.n_q_heads / c.n_kv_heads);
   }
@@ -1773,7 +1782,7 @@ OSPREY_API int osprey_verify_tree(osprey_handle* h, const osprey_verify_tree_arg
 struct osprey_graph {
   osprey_handle* h = nullptr;
   hipGraphExec_t exec = nullptr;
-  int B = 0, K = 0, taps_stride = 0;
+  int B = 0, K = 0, max_pending = 0;
   long max_context = 0;
   std::vector<int> slots;
 };
@@ -1813,6 +1822,13 @@ OSPREY_API int osprey_graph_capture(osprey_handle* h, const osprey_step_args* st
     if (graph_need(h, &probe, step->slots[b]) > max_context)
       return fail(OSPREY_E_CAPACITY, "slot %d already needs more than max_context %d positions", step->slots[b], max_context);
   }
+  // Rows per sequence that a launch may find pending: as many as the taps hold, for slots that
+  // longer drafts call by call left; what its own K leaves where the workspace holds no more.
+  int pend = std::min(step->taps_stride, h->cfg.max_k + 1);
+  if ((long)B * (pend + (mask_token >= 0 ? K - 1 : 0)) > h->D.Rmax) {
+    pend = K + 1;
+    for (int b = 0; b < B; ++b) pend = std::max(pend, h->slots[step->slots[b]].drafted_k + 1);
+  }
   // the calls below validate everything else and update the host state as if they ran:
   // keep that state and put it back afterwards (launches advance it)
   const std::vector<SlotHost> saved = h->slots;
@@ -1823,9 +1839,11 @@ OSPREY_API int osprey_graph_capture(osprey_handle* h, const osprey_step_args* st
   hipError_t e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return fail(OSPREY_E_DEVICE, "hipStreamBeginCapture: %s", hipGetErrorString(e));
   h->ctx_plan = max_context;
+  h->pend_plan = pend;
   rc = mask_token < 0 ? osprey_draft_step(h, step) : osprey_draft_block(h, step, mask_token);
   if (rc == OSPREY_OK) rc = osprey_verify(h, v);
   h->ctx_plan = 0;
+  h->pend_plan = 0;
   const std::string msg = g_err;
   hipGraph_t graph = nullptr;
   e = hipStreamEndCapture(h->stream, &graph);
@@ -1850,7 +1868,7 @@ OSPREY_API int osprey_graph_capture(osprey_handle* h, const osprey_step_args* st
   g->exec = exec;
   g->B = B;
   g->K = K;
-  g->taps_stride = step->taps_stride;
+  g->max_pending = pend;
   g->max_context = max_context;
   g->slots.assign(step->slots, step->slots + B);
   *out = g;
@@ -1864,9 +1882,9 @@ OSPREY_API int osprey_graph_launch(osprey_handle* h, osprey_graph* g) {
   for (int slot : g->slots) {
     const SlotHost& s = h->slots[slot];
     if (s.state != S_VERIFIED) return fail(OSPREY_E_STATE, "slot %d has no verified tokens pending", slot);
-    if (s.drafted_k + 1 > g->taps_stride)
-      return fail(OSPREY_E_INVALID, "slot %d: %d pending rows exceed the captured taps_stride %d", slot,
-                  s.drafted_k + 1, g->taps_stride);
+    if (s.drafted_k + 1 > g->max_pending)
+      return fail(OSPREY_E_INVALID, "slot %d: %d pending rows exceed the captured bound %d", slot,
+                  s.drafted_k + 1, g->max_pending);
     const long need = graph_need(h, g, slot);
     if (need > g->max_context || need > (long)s.nblocks * h->cfg.kv_block)
       return fail(OSPREY_E_CAPACITY, "slot %d: up to %ld positions exceed the graph's max_context %ld or its pages",

@@ -133,3 +133,68 @@ def test_graph_misuse_is_refused():
     st.synchronize()
     assert s.drafter.device_errors() == 0
     g.close()
+
+
+@pytest.mark.parametrize("name,k0", [("p_single128", 1), ("p_qwen_small", 2), ("p_tiny_f32", 1)])
+def test_graph_captured_after_a_shorter_draft(name, k0):
+    """A graph of K drafts captured while the slots hold what a call with fewer drafts left
+    pending: its later launches ingest up to K + 1 tokens each.  (The calls plan fewer rows
+    for the first iteration, so logits are compared within the parity tests' tolerances.)"""
+    _require_gpu()
+    from paper_2609_09338_amd import workload as WL
+    w = synth.get(name).with_(temps=(0.0,), draft_temps=(), sigma=0.01)
+    n_it, B = 5, w.batch
+    s = WL.make_drafter(w, n_it)
+    out = WL.alloc_outputs(s)
+    inps = [WL.iter_inputs(s, it) for it in range(n_it)]
+    short = dict(drafts=torch.empty((B, k0), dtype=torch.int32, device=s.device),
+                 mask=torch.empty((B, k0), dtype=torch.uint8, device=s.device),
+                 tokens=torch.empty((B, k0 + 1), dtype=torch.int32, device=s.device),
+                 logits=torch.empty((B, k0, w.vocab_draft), device=s.device))
+    targets = []
+
+    def first():
+        WL.reset_sequences(s)
+        dr, i = s.drafter, inps[0]
+        dr.draft_step(list(range(B)), k0, i.taps, s.draft_temperature, i.u_draft[:, :k0].contiguous(), n_new=[1] * B,
+                      new_tokens=i.new_tokens, taps_stride=w.K + 1, draft_tokens=short["drafts"],
+                      draft_logits=short["logits"])
+        if not targets:
+            full = torch.cat([short["logits"], short["logits"][:, -1:].expand(-1, w.K - k0, -1)], 1)
+            targets.append(WL.synthetic_target(s, 0, full.contiguous())[:, :k0 + 1].contiguous())
+        dr.verify(list(range(B)), k0, targets[0], s.temperature, i.u_accept[:, :k0].contiguous(), i.u_bonus,
+                  out.accept_len, short["mask"], short["tokens"], draft_temperature=s.draft_temperature)
+
+    first()
+    ref = []
+    for it in range(1, n_it):
+        WL.draft(s, it, inps[it], out)
+        targets.append(WL.synthetic_target(s, it, out.logits))
+        WL.verify(s, inps[it], targets[it], out)
+        torch.cuda.synchronize()
+        ref.append([t.clone() for t in (out.drafts, out.logits, out.accept_len, out.mask, out.tokens)])
+    accepted = [int(r[2].max()) for r in ref]
+    assert max(accepted[:-1]) > k0, accepted        # (else nothing would be cut short)
+    st = torch.cuda.Stream()
+    s.drafter.set_stream(st)
+    first()
+    st.synchronize()
+    fx = [torch.empty_like(t) for t in (inps[1].taps, inps[1].u_draft, targets[1], inps[1].u_accept, inps[1].u_bonus)]
+    _say(f"[graph] {name}: capture after {k0} drafts, accepted {accepted}")
+    g = s.drafter.capture_iteration(list(range(B)), w.K, fx[0], s.draft_temperature, fx[1], out.drafts, out.logits, fx[2],
+                                    s.temperature, fx[3], fx[4], out.accept_len, out.mask, out.tokens,
+                                    max_context=int(s.drafter.cfg.max_seq_len), taps_stride=w.K + 1)
+    for it in range(1, n_it):
+        i = inps[it]
+        with torch.cuda.stream(st):
+            for dst, src in zip(fx, (i.taps, i.u_draft, targets[it], i.u_accept, i.u_bonus)):
+                dst.copy_(src)
+        g.launch()
+        st.synchronize()
+        for got, want in zip((out.drafts, out.accept_len, out.mask, out.tokens), ref[it - 1][:1] + ref[it - 1][2:]):
+            assert torch.equal(got, want), (name, it)
+        m = torch.isfinite(ref[it - 1][1])
+        assert torch.equal(m, torch.isfinite(out.logits))
+        assert float((out.logits - ref[it - 1][1])[m].abs().max()) < (2e-2 if w.dtype == "bf16" else 1e-4)
+    assert s.drafter.device_errors() == 0
+    g.close()
