@@ -420,7 +420,8 @@ int osprey_device_errors(osprey_handle* h, uint32_t* flags);
  * event timing of family f on the handle's stream (0 disables; every call clears
  * the records).  Families: 0 = LM head (final norm + vocabulary GEMV + softmax
  * statistics), 1 = attention (split pass + split merge), 2 = verify (all its
- * kernels), 3 = a whole draft_step, 4 = expanded-QKV GEMV.  Each event adds a few
+ * kernels), 3 = a whole draft_step, 4 = expanded-QKV product (a long ingest's last layer
+ * has two: every row's keys and values, and the used rows' whole one).  Each event adds a few
  * microseconds of idle time to the stream, so time few families at once.  A timed
  * LM head, and a timed attention, runs 8 times back to back between its events
  * (the same outputs again), so its events' overhead is shared by 8 launches.

@@ -539,7 +539,9 @@ bool run_body(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const fl
       const size_t el = c.dtype == OSPREY_BF16 ? 2 : 4;
       kv.w0 = reinterpret_cast<const char*>(L.w_qkv) + el * nq * hd * 2 * d;
       kv.N = kv.ldy = 2 * nkv * hd;
+      const int t = h->t_begin(4);
       launch_gemv(c.dtype, SRC_QKV, EPI_STORE, kv, h->stream);
+      h->t_end(t);
       AttnArgs ka{};
       append_args(h, ka, rows, L, l, B == 1 ? slot0 : -1, W.bslot, W.qkv, 1, kv.N, 0);
       launch_rows_qkv(c.dtype, ka, nullptr, h->stream);
@@ -754,7 +756,9 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
       g.Kd = 2 * d;
       g.w0 = reinterpret_cast<const uint16_t*>(L.w_qkv) + (long)nq * hd * 2 * d;
       g.N = 2 * nkv * hd;
+      const int t = h->t_begin(4);
       const int ks = gemm(SRC_PREP, EPI_STORE, g);
+      h->t_end(t);
       AttnArgs a{};
       append_args(h, a, rows, L, l, (B == 1 && !tree) ? slot0 : -1, W.bslot, part, ks, g.N, (long)rows.max_rows * g.N);
       launch_rows_qkv(c.dtype, a, nullptr, h->stream);

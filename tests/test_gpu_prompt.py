@@ -160,3 +160,30 @@ def test_tree_after_a_prompt_matches_oracle(rows):
     if gk != ok:
         near = parity.tree_near_tie_keys(t, 4.0 * err + 1e-9)
         assert parity.tree_mismatch_excused(gk, ok, near), (g_tok, t.tokens)
+
+
+@pytest.mark.parametrize("body,rows,K,launches", [("p_qwen_small", 70, 1, 3), ("p_qwen_small", 64, 1, 2),
+                                                  ("p_qwen_small", 70, 0, 2), ("p_tiny_f32", 20, 1, 2)])
+def test_every_qkv_product_of_an_ingest_is_timed(body, rows, K, launches):
+    """A narrowed last layer has two: the keys and values of every row, and the used rows'."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import _lib as L
+    from paper_2609_09338_amd import workload as WL
+    from paper_2609_09338_amd.binding import KERNEL_QKV, Drafter, make_config
+    w = synth.get(body)
+    n = rows // 16 + 2
+    cfg = make_config(n_layers=w.n_layers, d_model=w.d_model, n_q_heads=w.n_q_heads, n_kv_heads=w.n_kv_heads,
+                      head_dim=w.head_dim, d_ffn=w.d_ffn, vocab_draft=w.vocab_draft, vocab_target=w.vocab_target,
+                      target_hidden=w.target_hidden, dtype=L.OSPREY_BF16 if w.dtype == "bf16" else L.OSPREY_F32,
+                      qk_norm=w.qk_norm, max_batch=1, max_k=1, max_seq_len=16 * n, kv_num_blocks=n, max_new_rows=rows)
+    dev = "cuda:0"
+    dr = Drafter(cfg, {k: WL.to_dev(v, w, dev) for k, v in synth.make_weights(w).items()},
+                 torch.from_numpy(synth.make_d2t(w)).to(dev))
+    dr.seq_reset(0, range(n))
+    dr.kernel_timing((KERNEL_QKV,))
+    print(f"[timing] {body} {rows} rows K {K}", flush=True)
+    dr.draft_step([0], K, WL.to_dev(synth.taps(w, 0, 0, rows), w, dev), torch.zeros(1, device=dev), n_new=[rows],
+                  new_tokens=torch.from_numpy(synth.prompt_tokens(w, 0, rows)).to(dev))
+    ms, got = dr.kernel_time(KERNEL_QKV)
+    assert got == launches and ms > 0
