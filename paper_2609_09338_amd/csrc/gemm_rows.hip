@@ -237,8 +237,8 @@ __global__ void __launch_bounds__(128 * WM, 2) k_gemm_rows(GemvArgs a, int mt, i
   }
 }
 
-// K splits: as many as it takes to give 256 CUs two blocks each (of 256 rows: one), of at
-// least four steps.
+// K splits: as many as it takes to give every CU two blocks (of 256 rows: one), of at least
+// four steps.
 static int gemm_rows_splits(int tiles, int blocks, int Kd, int& steps_per_split) {
   const int steps = Kd / kGrK;
   int ks = std::max(1, std::min(std::min(blocks / tiles, steps / 4), kMaxKSplit));
@@ -266,12 +266,12 @@ struct GrPlan {
   int mt, nt, ks, sps;
   double cost;
 };
-static GrPlan gr_plan(int wm, int rows, int N, int nper, int Kd) {
+static GrPlan gr_plan(int wm, int rows, int N, int nper, int Kd, int n_cu) {
   GrPlan p;
   p.mt = (rows + wm * kGrM - 1) / (wm * kGrM);
   p.nt = (N + nper - 1) / nper;
-  p.ks = gemm_rows_splits(p.mt * p.nt, wm == 4 ? 256 : 512, Kd, p.sps);
-  const int per_cu = ((p.mt * p.nt * p.ks) + 255) / 256;
+  p.ks = gemm_rows_splits(p.mt * p.nt, wm == 4 ? n_cu : 2 * n_cu, Kd, p.sps);
+  const int per_cu = (p.mt * p.nt * p.ks + n_cu - 1) / n_cu;
   p.cost = (wm == 4 ? 2 * 0.93 : 1.0) * per_cu * p.sps;
   return p;
 }
@@ -291,16 +291,16 @@ static int launch_tile(const GemvArgs& a, const GrPlan& p, hipStream_t st) {
 // rows) and 330 for the taps (598 -> 685 us), 300 rows leave 40% of two empty (a whole
 // prompt 208 -> 225 us).
 template <int SRC, int EPI>
-static int launch_t(const GemvArgs& a, hipStream_t st) {
+static int launch_t(const GemvArgs& a, int n_cu, hipStream_t st) {
   const int nper = EPI == EPI_SWIGLU ? kGrN / 2 : kGrN;
-  const GrPlan wide = gr_plan(4, a.max_rows, a.N, nper, a.Kd), half = gr_plan(2, a.max_rows, a.N, nper, a.Kd);
+  const GrPlan wide = gr_plan(4, a.max_rows, a.N, nper, a.Kd, n_cu), half = gr_plan(2, a.max_rows, a.N, nper, a.Kd, n_cu);
   return wide.cost < half.cost ? launch_tile<SRC, EPI, 4>(a, wide, st) : launch_tile<SRC, EPI, 2>(a, half, st);
 }
 
-int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st) {
-  if (src == SRC_TAPS) return launch_t<SRC_TAPS, EPI_STORE>(a, st);
-  if (epi == EPI_SWIGLU) return launch_t<SRC_PREP, EPI_SWIGLU>(a, st);
-  return launch_t<SRC_PREP, EPI_STORE>(a, st);
+int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, int n_cu, hipStream_t st) {
+  if (src == SRC_TAPS) return launch_t<SRC_TAPS, EPI_STORE>(a, n_cu, st);
+  if (epi == EPI_SWIGLU) return launch_t<SRC_PREP, EPI_SWIGLU>(a, n_cu, st);
+  return launch_t<SRC_PREP, EPI_STORE>(a, n_cu, st);
 }
 
 }  // namespace osp

@@ -166,9 +166,9 @@ int launch_gemm(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st);
 // The same for large passes (more than 128 rows) of the shapes it supports (EPI_STORE,
 // EPI_SWIGLU): large tiles, K split only where the tiles leave the chip idle.  Returns the
 // K splits written to split_buf, or 0 when silu(g) u went to act_hi / act_lo instead.
-// input_rows: bound on the row indices read.
+// input_rows: bound on the row indices read; n_cu: the device's CUs.
 bool gemm_rows_supported(SrcKind src, const GemvArgs& a, long input_rows);
-int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, hipStream_t st);
+int launch_gemm_rows(SrcKind src, EpiKind epi, const GemvArgs& a, int n_cu, hipStream_t st);
 // True when a pass of `rows` rows takes the matrix-core path.
 bool gemm_use_mfma(int wdtype, int rows);
 int gemm_rows_per_block(EpiKind epi);

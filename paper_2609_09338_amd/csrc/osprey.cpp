@@ -692,9 +692,10 @@ int stream_product(SrcKind src, const GemvArgs& g, hipStream_t st) {
 // A product of a pass of more than kLmMaxRows rows: up to kSkMaxRows prepared rows stream the
 // weights once (width 1024, 96 rows: 10.5 us a product against 12.1 of gemm_mfma.h's two
 // 64-row blocks), larger passes take the tiled products.
-int gemm_large(SrcKind src, EpiKind epi, const GemvArgs& g, long input_rows, hipStream_t st) {
-  if (src == SRC_PREP && g.max_rows <= kSkMaxRows) return stream_product(src, g, st);
-  return gemm_rows_supported(src, g, input_rows) ? launch_gemm_rows(src, epi, g, st) : launch_gemm(src, epi, g, st);
+int gemm_large(const osprey_handle* h, SrcKind src, EpiKind epi, const GemvArgs& g, long input_rows) {
+  if (src == SRC_PREP && g.max_rows <= kSkMaxRows) return stream_product(src, g, h->stream);
+  if (gemm_rows_supported(src, g, input_rows)) return launch_gemm_rows(src, epi, g, h->n_cu, h->stream);
+  return launch_gemm(src, epi, g, h->stream);
 }
 
 // `keep` as in run_body.
@@ -709,7 +710,7 @@ bool run_body_mr(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const
   float* part = skinny ? W.split_s : W.split;
   auto gemm = [&](SrcKind src, EpiKind epi, GemvArgs& g) -> int {
     g.split_buf = part;
-    return skinny ? stream_product(src, g, h->stream) : gemm_large(src, epi, g, rows.max_rows, h->stream);
+    return skinny ? stream_product(src, g, h->stream) : gemm_large(h, src, epi, g, rows.max_rows);
   };
   const int d = c.d_model, hd = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads, F = c.d_ffn;
   const int qkv_w = h->D.qkv_rows;
@@ -1456,7 +1457,7 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
     } else {
       // (tap rows: b taps_stride + j, or packed)
       const long tap_rows = a->taps_stride > 0 ? (long)B * a->taps_stride : rows;
-      ks_taps = gemm_large(SRC_TAPS, EPI_STORE, gt, tap_rows, h->stream);
+      ks_taps = gemm_large(h, SRC_TAPS, EPI_STORE, gt, tap_rows);
     }
     narrow = run_body_mr(h, ing, W.cu, B, nullptr, ks_taps, split, max_new + (block_mask >= 0 ? extra : 0),
                          a->slots[0], nullptr, nullptr, keep);
