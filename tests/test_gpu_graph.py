@@ -44,11 +44,14 @@ def _reference(w, n_it):
     return s, out, rec
 
 
-@pytest.mark.parametrize("name", ["p_qwen_small", "p_single128", "p_block"])
-def test_graph_replays_equal_stream_launches(name):
+# (twelve sequences: an ingest of 72 planned rows narrows its last layer)
+@pytest.mark.parametrize("name,batch", [("p_qwen_small", 3), ("p_single128", 1), ("p_block", 3), ("p_qwen_small", 12)])
+def test_graph_replays_equal_stream_launches(name, batch):
     _require_gpu()
     from paper_2609_09338_amd import workload as WL
     w = synth.get(name)
+    if batch != w.batch:
+        w = w.with_(batch=batch)
     n_it = 5
     _say(f"[graph] {name}: stream reference")
     s, out, rec = _reference(w, n_it)

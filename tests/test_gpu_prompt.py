@@ -162,6 +162,40 @@ def test_tree_after_a_prompt_matches_oracle(rows):
         assert parity.tree_mismatch_excused(gk, ok, near), (g_tok, t.tokens)
 
 
+def test_taps_past_two_gigabytes():
+    """Tap rows further apart than a 31-bit byte offset reaches take the other product."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import _lib as L
+    from paper_2609_09338_amd import workload as WL
+    from paper_2609_09338_amd.binding import Drafter, make_config
+    w = synth.get("p_qwen_small").with_(batch=2)
+    dev, rows = "cuda:0", [100, 61]
+    stride = (1 << 31) // (2 * 2 * w.tap_width) + 1
+    weights, d2t = synth.make_weights(w), synth.make_d2t(w)
+    cfg = make_config(n_layers=w.n_layers, d_model=w.d_model, n_q_heads=w.n_q_heads, n_kv_heads=w.n_kv_heads,
+                      head_dim=w.head_dim, d_ffn=w.d_ffn, vocab_draft=w.vocab_draft, vocab_target=w.vocab_target,
+                      target_hidden=w.target_hidden, dtype=L.OSPREY_BF16, qk_norm=w.qk_norm, max_batch=2, max_k=1,
+                      max_seq_len=112, kv_num_blocks=14, max_new_rows=sum(rows))
+    dr = Drafter(cfg, {k: WL.to_dev(v, w, dev) for k, v in weights.items()}, torch.from_numpy(d2t).to(dev))
+    toks = [synth.prompt_tokens(w, b, n) for b, n in enumerate(rows)]
+    taps = [synth.taps(w, 0, b, n) for b, n in enumerate(rows)]
+    far = torch.empty((2, stride, w.tap_width), dtype=torch.bfloat16, device=dev)
+    for b, n in enumerate(rows):
+        dr.seq_reset(b, range(7 * b, 7 * b + 7))
+        far[b, :n] = WL.to_dev(taps[b], w, dev)
+    logits = torch.empty((2, 1, w.vocab_draft), device=dev)
+    print("[prompt] taps past 2 GB", flush=True)
+    dr.draft_step([0, 1], 1, far, torch.zeros(2, device=dev), n_new=rows, taps_stride=stride, draft_logits=logits,
+                  new_tokens=torch.from_numpy(np.concatenate(toks).astype(np.int32)).to(dev))
+    torch.cuda.synchronize()
+    assert dr.device_errors() == 0
+    o = OH.build_drafter(w, weights, d2t)
+    for b, n in enumerate(rows):
+        _, want, _, _ = o.draft(OH.Sequence(w, n + 1), toks[b], taps[b].astype(np.float64), 1, 0.0, np.zeros(1))
+        assert np.max(np.abs(logits[b].cpu().numpy() - want)) < 2e-2
+
+
 @pytest.mark.parametrize("body,rows,K,launches", [("p_qwen_small", 70, 1, 3), ("p_qwen_small", 64, 1, 2),
                                                   ("p_qwen_small", 70, 0, 2), ("p_tiny_f32", 20, 1, 2)])
 def test_every_qkv_product_of_an_ingest_is_timed(body, rows, K, launches):

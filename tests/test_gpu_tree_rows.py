@@ -1,6 +1,6 @@
-"""Selection of a draft tree's children where the likely ids are not spread over the
-LM-head rows: equal logits, neighbouring ids, and maps that reach few rows.  The lower row
-comes first on equal logits."""
+"""Draft trees against the oracle: selection of children where the likely ids are not spread
+over the LM-head rows (equal logits, neighbouring ids, maps that reach few rows; the lower
+row comes first on equal logits), and frontiers that attend by blocks of query vectors."""
 import numpy as np
 import pytest
 import torch
@@ -109,6 +109,52 @@ def test_tree_of_ties_and_neighbours_matches_oracle(name, topk, depth, nodes, B)
             # (only where two different logits or scores were closer than four times that)
             near = parity.tree_near_tie_keys(t, 4.0 * err + 1e-9, equal=False)
             assert parity.tree_mismatch_excused(gk, ok, near), (b, tk[b], t.tokens, pr[b], t.parents, err)
+            flagged += 1
+    assert flagged <= 1
+
+
+@pytest.mark.parametrize("wl,topk", [("p_single64", 5), ("p_single64", 6), ("p_inject", 8)])
+def test_tree_rows_by_blocks_of_query_vectors_match_oracle(wl, topk):
+    """Frontiers of more than 16 query vectors per kv head (topk rows of 4 heads) attend to
+    the committed context by blocks of vectors, over one and over several splits."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import workload as WL
+    w = synth.get(wl)
+    weights, d2t = synth.make_weights(w), synth.make_d2t(w)
+    ctx, R, depth, nodes = [0, 33, 1100], 3, 4, 30
+    B = len(ctx)
+    dr = _drafter(w, weights, d2t, B, max(ctx) + R + depth, topk)
+    kv = []
+    for b, c in enumerate(ctx):
+        kv.append(synth.context_kv(w, b, c))
+        if c:
+            dr.kv_append(b, *(WL.to_dev(x, w, "cuda:0") for x in kv[b]))
+    toks = [synth.prompt_tokens(w, b, R) for b in range(B)]
+    taps = [synth.taps(w, 0, b, R) for b in range(B)]
+    tk = torch.empty((B, nodes), dtype=torch.int32, device="cuda:0")
+    pr = torch.empty_like(tk)
+    sc = torch.empty((B, nodes), dtype=torch.float64, device="cuda:0")
+    print(f"[tree by blocks] {wl} topk {topk}", flush=True)
+    dr.draft_tree(list(range(B)), topk, depth, nodes, WL.to_dev(np.concatenate(taps), w, "cuda:0"),
+                  torch.zeros(B, device="cuda:0"), tk, pr, n_new=[R] * B,
+                  new_tokens=torch.from_numpy(np.concatenate(toks)).to("cuda:0"), scores=sc)
+    torch.cuda.synchronize()
+    assert dr.device_errors() == 0
+    tk, pr, sc = tk.cpu().numpy(), pr.cpu().numpy(), sc.cpu().numpy()
+    o = OH.build_drafter(w, weights, d2t)
+    flagged = 0
+    for b, c in enumerate(ctx):
+        seq = OH.Sequence(w, c + R + depth + 1)
+        seq.k[:, :c], seq.v[:, :c], seq.length = *kv[b], c
+        t = draft_tree(o, seq, toks[b], taps[b].astype(np.float64), topk, depth, nodes)
+        gk, ok = _path_keys(tk[b], pr[b]), _path_keys(t.tokens, t.parents)
+        want = dict(zip(ok, t.scores))
+        err = max(abs(v - want[k]) for k, v in zip(gk, sc[b]) if k in want)
+        print(f"[tree by blocks] context {c}: score error {err:.1e}, equal {gk == ok}", flush=True)
+        assert err < 2e-2
+        if gk != ok:
+            assert parity.tree_mismatch_excused(gk, ok, parity.tree_near_tie_keys(t, 4.0 * err + 1e-9)), (tk[b], t.tokens)
             flagged += 1
     assert flagged <= 1
 
