@@ -379,7 +379,7 @@ constexpr long kKvStreamBytes = 160L << 20;   // pages of a pass over every laye
 struct SplitPlan {
   int n_split, split_len;
   bool kv_stream;   // the context's pages over every layer outsize the last-level cache
-  long ctx_total;   // positions of all sequences
+  long ctx_max, ctx_total;   // positions of the longest sequence, of all
   long tile_ctx;    // the ingest's blocks of query vectors per kv head, times their contexts
 };
 SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int max_split = kMaxSplit,
@@ -394,6 +394,7 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
   len = std::min<long>(len, kMaxSplitLen);
   len = (len + 15) / 16 * 16;
   SplitPlan p;
+  p.ctx_max = ctx_max;
   p.ctx_total = ctx_total;
   p.tile_ctx = 0;
   p.split_len = (int)len;
@@ -433,8 +434,8 @@ SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, in
   SplitPlan p = sp;
   long len = (ctx + n - 1) / n;
   const long work = tree ? sp.ctx_total * per_seq : sp.tile_ctx;
-  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu);
-  len = std::min(len, std::max(2 * even, kRowSplitLen));
+  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu) * ctx / sp.ctx_max;   // (in the splits' whole lengths)
+  len = std::min(len, std::max(2 * even, 2 * kRowSplitLen));
   len = std::max(len, (ctx + max_split - 1) / max_split);
   len = (len + 63) / 64 * 64;
   p.split_len = (int)len;
