@@ -379,6 +379,8 @@ constexpr long kKvStreamBytes = 160L << 20;   // pages of a pass over every laye
 struct SplitPlan {
   int n_split, split_len;
   bool kv_stream;   // the context's pages over every layer outsize the last-level cache
+  // of the contexts at hand, also where the plan covers longer ones (graph capture):
+  long ctx;                  // the splits' whole lengths, at least the longest context
   long ctx_max, ctx_total;   // positions of the longest sequence, of all
   long tile_ctx;    // the ingest's blocks of query vectors per kv head, times their contexts
 };
@@ -399,6 +401,7 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
   p.tile_ctx = 0;
   p.split_len = (int)len;
   p.n_split = (int)std::max<long>(1, (ctx_max + len - 1) / len);
+  p.ctx = (long)p.n_split * p.split_len;
   // Pages that cannot stay in the 256 MB last-level cache from one pass to the next are
   // read non-temporally (faster, and the weights stay cached); a smaller context is
   // read again by every draft step and keeps plain loads.
@@ -410,7 +413,7 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
 // Context splits of a pass whose attention runs by blocks of query vectors: none while
 // the tiles of vectors give the chip three and a half blocks per CU by themselves (two run
 // at once; causal tiles differ in length, so the rest balances them); else as many pieces of
-// at least kRowSplitLen positions as stay below that.  Whole calls with 1 / 2 / 3 / 4 / 6 / 8
+// at least 128 or 192 positions as stay below that.  Whole calls with 1 / 2 / 3 / 4 / 6 / 8
 // splits: a 1999-token prompt (256 tiles) 480 / 473 / 461 / 468 / 465 / 470 us, two turns of
 // 770 tokens over 7000 positions (104) 754 / 643 / 588 / 601 / 580 / 585, four prompts of
 // 3600 tokens (450) 649 / 680 / 676 / 684 / 687 / 699.
@@ -419,27 +422,33 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
 // that bound.)  Ingests of 16 rows for 64 sequences, one over 131000 positions and 63 over 512,
 // with their first drafts and verification 3913 -> 1081 us (chains of two, d 2560: 6676 -> 3756);
 // with a longest context of 32768 3718 -> 3036, eight prompts beside one such turn 1680 -> 1429.
-constexpr long kRowSplitLen = 128;
+// Few tiles take pieces of one length whatever the context, and a captured pass those of the
+// contexts at hand (more of them, for the contexts it covers): a graph's launches and the same
+// calls one by one then sum in the same order, and give the same bits.  The pieces are longer
+// once they would be more than a block per CU: calls with a 17-row block (8 kv heads) in pieces
+// of 128 / 192 take 460 / 464 us over 2048 positions, 470 / 472 over 4000, 479 / 471 over 4300,
+// 487 / 477 over 6000.
+constexpr long kRowSplitLen = 128, kRowSplitLong = 192;
 SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, int rows_per_seq, int rows,
                           bool tree) {
   const osprey_config& c = h->cfg;
   const int group = c.n_q_heads / c.n_kv_heads;
-  const long ctx = (long)sp.n_split * sp.split_len;   // at least the longest context
+  const long cover = std::max(sp.ctx, (long)sp.n_split * sp.split_len);
   // a batch's tiles: the longest sequence's, and no more than its rows fill
   const int per_seq = attn_rows_tiles(rows_per_seq, rows_per_seq, group);
   const long tiles = std::min<long>((long)B * per_seq, (long)attn_rows_tiles(rows, rows_per_seq, group) + B);
   const int max_split = tree ? kMaxSplit - 1 : kMaxSplit;   // (a tree row's own branch is one more)
-  long n = 7L * h->n_cu / (2 * tiles * c.n_kv_heads);
-  n = std::max<long>(1, std::min<long>(std::min<long>(n, max_split), ctx / kRowSplitLen));
-  SplitPlan p = sp;
-  long len = (ctx + n - 1) / n;
+  const long n = std::max<long>(1, std::min<long>(7L * h->n_cu / (2 * tiles * c.n_kv_heads), max_split));
+  const bool few = tiles * c.n_kv_heads * ((sp.ctx + kRowSplitLen - 1) / kRowSplitLen) <= h->n_cu;
+  long len = std::max((sp.ctx + n - 1) / n, few ? kRowSplitLen : kRowSplitLong);
   const long work = tree ? sp.ctx_total * per_seq : sp.tile_ctx;
-  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu) * ctx / sp.ctx_max;   // (in the splits' whole lengths)
+  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu) * sp.ctx / sp.ctx_max;   // (in the splits' whole lengths)
   len = std::min(len, std::max(2 * even, 2 * kRowSplitLen));
-  len = std::max(len, (ctx + max_split - 1) / max_split);
+  len = std::max(len, (cover + max_split - 1) / max_split);
   len = (len + 63) / 64 * 64;
+  SplitPlan p = sp;
   p.split_len = (int)len;
-  p.n_split = (int)((ctx + len - 1) / len);
+  p.n_split = (int)((cover + len - 1) / len);
   return p;
 }
 
@@ -1373,22 +1382,22 @@ int step_ingest(osprey_handle* h, const osprey_step_args* a, int K, int extra, S
     return fail(OSPREY_E_CAPACITY, "%ld new rows exceed max_new_rows", rows);
 
   const Ws& W = h->W;
-  if (h->ctx_plan > 0) {
-    ctx_max = std::max(ctx_max, h->ctx_plan);
-    ctx_total = std::max(ctx_total, h->ctx_plan * B);
-  }
+  const long ctx_plan = std::max(ctx_max, h->ctx_plan), total_plan = std::max(ctx_total, h->ctx_plan * B);
   // A single sequence's bf16 chain takes splits of at least 128 positions: its draft
   // steps attend faster over a 2K context in 17 splits than in 33, and their O
   // projection merges that few splits itself.  (Block passes and fp32 caches, whose
   // attention only loses by it, and trees keep 64.)
   const bool chain1 = B == 1 && c.dtype == OSPREY_BF16 && block_mask < 0 && K >= 2;
-  split = plan_splits(h, ctx_max, ctx_total, max_split, chain1 ? 128 : 64);
+  split = plan_splits(h, ctx_plan, total_plan, max_split, chain1 ? 128 : 64);
   if (split.n_split > max_split)
-    return fail(OSPREY_E_UNSUPPORTED, "a context of %ld positions needs %d splits (at most %d)", ctx_max,
+    return fail(OSPREY_E_UNSUPPORTED, "a context of %ld positions needs %d splits (at most %d)", ctx_plan,
                 split.n_split, max_split);
+  split.ctx = plan_splits(h, ctx_max, ctx_total, max_split, chain1 ? 128 : 64).ctx;
+  split.ctx_max = ctx_max;
+  split.ctx_total = ctx_total;
   for (int b = 0; b < B; ++b) {
     const int n = planned_rows(h, a, b);
-    const long need = std::max(h->slots[a->slots[b]].len_max + n + extra, h->ctx_plan);
+    const long need = h->slots[a->slots[b]].len_max + n + extra;
     const int tail = block_mask >= 0 ? extra : 0;
     split.tile_ctx += need * attn_rows_tiles(n + tail, max_new + tail, c.n_q_heads / c.n_kv_heads);
   }

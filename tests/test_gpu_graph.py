@@ -44,14 +44,17 @@ def _reference(w, n_it):
     return s, out, rec
 
 
-# (twelve sequences: an ingest of 72 planned rows narrows its last layer)
-@pytest.mark.parametrize("name,batch", [("p_qwen_small", 3), ("p_single128", 1), ("p_block", 3), ("p_qwen_small", 12)])
-def test_graph_replays_equal_stream_launches(name, batch):
+# (twelve sequences: an ingest of 72 planned rows narrows its last layer; contexts of 1100:
+# ingests that attend by blocks of query vectors over several splits, planned for the longer
+# contexts of a graph)
+@pytest.mark.parametrize("name,change", [("p_qwen_small", {}), ("p_single128", {}), ("p_block", {}),
+                                         ("p_qwen_small", dict(batch=12)), ("p_block", dict(ctx_lo=1090, ctx_hi=1100)),
+                                         ("p_single64", dict(ctx_lo=1100, ctx_hi=1100)),
+                                         ("p_block", dict(batch=1, ctx_lo=2040, ctx_hi=2040))])
+def test_graph_replays_equal_stream_launches(name, change):
     _require_gpu()
     from paper_2609_09338_amd import workload as WL
-    w = synth.get(name)
-    if batch != w.batch:
-        w = w.with_(batch=batch)
+    w = synth.get(name).with_(**change)
     n_it = 5
     _say(f"[graph] {name}: stream reference")
     s, out, rec = _reference(w, n_it)
