@@ -22,14 +22,14 @@
 // The matrix cores bound it (four products per score and value, hi and lo): registers
 // hold two wavefronts per SIMD, so one's softmax overlaps another's products.
 // Blocks are kv head, sequence, row tile (one grid dimension, the head innermost) and
-// context split: heads go to the XCDs in turn, so each L2 holds the pages of the heads it serves, and the tiles of the longest
-// contexts start first.  With one split the output is written directly (hi / lo pairs);
-// a pass of too few tiles to fill the chip splits its context, and the merge kernel or
-// the O projection joins the partials.
-// Measured per layer: one 1999-token prompt (16 / 8 heads x 128) 1422 -> 78 us; four of 8200
-// tokens in all (32 / 8 heads x 128) 5850 -> 586 us; two turns of 770 tokens over 6000-8000
-// cached positions (16 / 8 x 128) 672 -> 216 us; a 17-row block (32 / 8 x 64) 24.2 -> 12.3 us.
-// Page-table entries ahead of the loop and values in pairs: the two turns' call 598 -> 585 us.
+// context split: heads go to the XCDs in turn, so each L2 holds the pages of the heads it
+// serves, and the tiles of the longest contexts start first.  With one split the output is
+// written directly (hi / lo pairs); a pass of too few tiles to fill the chip splits its
+// context, and the merge kernel or the O projection joins the partials.
+// Measured per layer, k_attn_mfma / this: one 1999-token prompt (16 / 8 heads x 128) 1422 / 65
+// us; four of 8200 tokens in all (32 / 8 heads x 128) 5600 / 608 us; two turns of 770 tokens
+// over 6000-8000 cached positions (16 / 8 x 128) 672 / 182 us; a 17-row block (32 / 8 x 64) 24.2
+// / 11.9 us.
 // (rocprofv3, the two turns: matrix cores busy 23% of the time, 3.4 vector instructions per
 // product; on average one wavefront per SIMD of the two that fit.)
 #include "common.h"

@@ -1,4 +1,4 @@
-// Tiled matrix-core products for passes of more than 64 rows (prompts, large batches):
+// Tiled matrix-core products for passes of more than 128 rows (prompts, large batches):
 // Y[r][n] = sum_c X[r][c] W[n][c], bf16 weights, X as bf16 hi / lo pairs (taps: bf16).
 //
 // The kernel of gemm_mfma.h gives every 64 rows a block of their own, whose weights go
@@ -11,8 +11,9 @@
 // 16 fragments from LDS for 64 products, about half of what the LDS delivers in that time.
 // 128-row blocks run two to a CU with two stages each (64 KB of LDS, 2 wavefronts per SIMD)
 // and cover each other's barriers, but a copy has one step to arrive; 256-row blocks have the
-// CU to themselves, three stages (144 KB), and wait only for copies requested two steps
-// before.  16-byte pieces are permuted within a row by the row, so that the 16 rows of a
+// CU to themselves and three stages (144 KB), so that a copy has two steps: each step waits
+// for copies requested two steps before (in one step of three the compiler, which cannot tell
+// the stages apart there, adds a wait for those of one step before).  16-byte pieces are permuted within a row by the row, so that the 16 rows of a
 // fragment read fall into different banks.
 //
 // The weights are the A operand, so a lane ends with four consecutive output columns of
@@ -21,11 +22,14 @@
 // projection's hi / lo input without the row kernel and its 2 x 2 F floats per row.
 // Blocks go to the XCDs in contiguous ranges of tiles, 1024 rows by rising weight
 // tile, so that an XCD's blocks share inputs and weights in its L2.
-// Bound by the matrix cores (two products per weight: hi and lo inputs).  Measured, before
-// and after: gate/up of 8200 rows (2 x 9728 x 2560) 4256 us and 1358 us of SwiGLU rows ->
-// 1325 us (1.23 PFLOP/s of products; a large library bf16 product reaches 1.22 on this
-// card), QKV (6144 x 5120) 2435 -> 939 us, taps (2560 x 12288) 2226 -> 599 us; 1999 rows
-// of the 1024-wide body: QKV 176 -> 60, gate/up 114 + 32 -> 59, down 66 -> 39, taps 226 -> 69.
+// Bound by the matrix cores (two products per weight: hi and lo inputs).  Measured, the kernel
+// of gemm_mfma.h / this one: gate/up of 8200 rows (2 x 9728 x 2560) 4256 us and 1358 us of
+// SwiGLU rows / 1258 us (1.30 PFLOP/s of products; a large library bf16 product reaches 1.19 on
+// this card), QKV (6144 x 5120) 2435 / 939 us, taps (2560 x 12288) 2226 / 580 us; 1999 rows of
+// the 1024-wide body: QKV 176 / 60, gate/up 114 + 32 / 61, down 66 / 39, taps 226 / 62.
+// K is summed whole in fp32 instead of in 256-column partials: keys and values of prompts next
+// to a rounding boundary fall to the other bf16 neighbour, and a prompt's distance from 64 bits
+// goes from 1.19e-4 to 1.24e-4 (1999 tokens) and from 1.75e-4 to 1.79e-4 (8200, d 2560).
 #include "common.h"
 #include "internal.h"
 
@@ -285,8 +289,8 @@ static int launch_tile(const GemvArgs& a, const GrPlan& p, hipStream_t st) {
   return fused ? 0 : p.ks;
 }
 
-// 256-row blocks run a step 7% faster per row (gate/up of 8200 rows, d 2560: 1343 -> 1279 us;
-// taps of 1999 rows, d 1024: 74.5 -> 62.5) where they fill their rounds of 256 CUs as well:
+// 256-row blocks run a step 7% faster per row (gate/up of 8200 rows, d 2560: 1343 / 1258 us;
+// taps of 1999 rows, d 1024: 74.5 / 62) where they fill their rounds of 256 CUs as well:
 // 8200 rows make 792 of them for QKV (four rounds, 3.09 full: 20% slower than 1560 of 128
 // rows) and 330 for the taps (598 -> 685 us), 300 rows leave 40% of two empty (a whole
 // prompt 208 -> 225 us).

@@ -442,7 +442,8 @@ SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, in
   const bool few = tiles * c.n_kv_heads * ((sp.ctx + kRowSplitLen - 1) / kRowSplitLen) <= h->n_cu;
   long len = std::max((sp.ctx + n - 1) / n, few ? kRowSplitLen : kRowSplitLong);
   const long work = tree ? sp.ctx_total * per_seq : sp.tile_ctx;
-  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu) * sp.ctx / sp.ctx_max;   // (in the splits' whole lengths)
+  // (an even deal, in the splits' whole lengths)
+  const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu) * sp.ctx / sp.ctx_max;
   len = std::min(len, std::max(2 * even, 2 * kRowSplitLen));
   len = std::max(len, (cover + max_split - 1) / max_split);
   len = (len + 63) / 64 * 64;
@@ -506,9 +507,9 @@ void append_args(osprey_handle* h, AttnArgs& a, const RowMeta& rows, const ospre
 // (a single sequence's draft step): layer 0 draws the step's token itself.
 // `keep`: the rows whose output is used: -1 every row, 0 none (an ingest without drafts:
 // the last layer ends with its keys and values), B each sequence's last row (W.last_row):
-// where it pays (narrow.h) an ingest then appends the last layer's keys and values for every row and runs its
-// attention, FFN and norm on B rows, left in rows 0 .. B - 1 (no later step reads another
-// row).  Whole calls: a 1999-token prompt 742 -> 497 us, four prompts of 8200 tokens (d 2560)
+// where it pays (narrow.h) an ingest then appends the last layer's keys and values for every
+// row and runs its attention, FFN and norm on B rows, left in rows 0 .. B - 1 (no later step
+// reads another row).  Whole calls: a 1999-token prompt 742 -> 497 us, four prompts of 8200 tokens (d 2560)
 // 10.6 -> 7.1 ms, two turns of 770 tokens 864 -> 625 us, a 128-token prompt and two fp32
 // chains 866 -> 548 us.  True when it did so (or keep is 0).
 bool run_body(osprey_handle* h, RowMeta rows, const int32_t* cu, int B, const float* s,

@@ -89,8 +89,8 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
   const int ntiles = max(0, min(min(T, TMAX), nt16 - t0));
   const int k_lo = EPI == SK_PART ? blockIdx.y * kc : 0;
   const int k_hi = EPI == SK_PART ? min(a.Kd, k_lo + kc) : a.Kd;
-  // units per tile and phase (96 rows: phases of one unit; attention outputs: one 256-column unit, a constant, so that
-  // the prefetch below is known to be a single unit)
+  // units per tile and phase (96 rows: phases of one unit; attention outputs: one 256-column
+  // unit, a constant, so that the prefetch below is known to be a single unit)
   const int nch = EPI == SK_PART && MT < 6 ? (SRC == SK_ATTN ? 1 : kc / kSkUnit) : NCH;
   // LM head blocks with no tile at all leave at once (block-uniform, before any barrier)
   if (EPI == SK_LOGITS && blockIdx.x * kSkWaves * T >= nt16) return;

@@ -19,12 +19,11 @@
 // list of them reaches the bound: then the k ranges of largest max are read, and rounds of
 // the wavefront's best pick the ranges and their logits.  Bound by the latency of dependent
 // steps: records, logits, candidates, d2t and scores, rows, the copy of the conditioning rows.
-// (One sequence of 4 rows: 14.6 us, 20.9 for a separate pass over every logit and a step that
-// merged its blocks; 12 sequences of 8 rows: 20 us, 65 for rounds over 32 records and 32 logits
-// of every lane for two rows per wavefront.  Whole calls with trees, start of that change /
-// likely ids spread / neighbours, copies or few mapped rows: one sequence 757 / 728 / 753-758 us,
-// 12 sequences 2190 / 1645 / 1736-1754; such rows once fell back to one wavefront scanning
-// 151936 logits, 1913-3642 and 6821-7030 us.)
+// (One sequence of 4 rows: 15 us, 21 for a separate pass over every logit and a step that
+// merged its blocks; 12 sequences of 8 rows: 21 us, 65 for rounds over 32 records and 32 logits
+// of every lane for two rows per wavefront.  Whole calls with likely ids spread / neighbours,
+// copies or few mapped rows: one sequence 728 / 753-758 us, 12 sequences 1645 / 1736-1754; one
+// wavefront scanning a row's 151936 logits in the latter cases took 1913-3642 and 6821-7030 us.)
 // A frontier row's attention over its ancestors' and its own keys/values (the tree
 // cache) is one more split of the context attention, added by the split combine.
 #include "common.h"
