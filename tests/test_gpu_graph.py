@@ -44,11 +44,11 @@ def _reference(w, n_it):
     return s, out, rec
 
 
-# (twelve sequences: an ingest of 72 planned rows narrows its last layer; contexts of 1100:
+# (twelve sequences: an ingest of 72 planned rows narrows its last layer, as 17 fp32 rows do; contexts of 1100:
 # ingests that attend by blocks of query vectors over several splits, planned for the longer
 # contexts of a graph)
 @pytest.mark.parametrize("name,change", [("p_qwen_small", {}), ("p_single128", {}), ("p_block", {}),
-                                         ("p_qwen_small", dict(batch=12)), ("p_block", dict(ctx_lo=1090, ctx_hi=1100)),
+                                         ("p_qwen_small", dict(batch=12)), ("p_tiny_f32", dict(K=16)), ("p_block", dict(ctx_lo=1090, ctx_hi=1100)),
                                          ("p_single64", dict(ctx_lo=1100, ctx_hi=1100)),
                                          ("p_block", dict(batch=1, ctx_lo=2040, ctx_hi=2040))])
 def test_graph_replays_equal_stream_launches(name, change):

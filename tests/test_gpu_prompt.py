@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 # name -> body, head dim and group; rows per sequence over each cached context.  A block
 # holds 64 or 128 query vectors (rows x group), a step 64 positions, a product tile 128 rows.
 CASES = {
+    "one_row": ("p_single64", [(5, 1)]),       # the vector body of bf16 weights
     "group2_hd64": ("p_qwen_small", [(0, 9), (0, 33), (47, 64)]),
     "group2_hd64_ragged": ("p_qwen_small", [(0, 128), (129, 1), (16, 200)]),
     "group4_hd64_one": ("p_single64", [(300, 37)]),
