@@ -417,11 +417,12 @@ SplitPlan plan_splits(const osprey_handle* h, long ctx_max, long ctx_total, int 
 // splits: a 1999-token prompt (256 tiles) 480 / 473 / 461 / 468 / 465 / 470 us, two turns of
 // 770 tokens over 7000 positions (104) 754 / 643 / 588 / 601 / 580 / 585, four prompts of
 // 3600 tokens (450) 649 / 680 / 676 / 684 / 687 / 699.
-// A long context among short ones is cut further: no block walks more than twice the
-// positions that an even deal of the pass's work would give it.  (Equal contexts never reach
-// that bound.)  Ingests of 16 rows for 64 sequences, one over 131000 positions and 63 over 512,
-// with their first drafts and verification 3913 -> 1081 us (chains of two, d 2560: 6676 -> 3756);
-// with a longest context of 32768 3718 -> 3036, eight prompts beside one such turn 1680 -> 1429.
+// A long context among short ones is cut further: no block walks more than four times the
+// positions that an even deal of the pass's work would give it (twice would cut prompts of 763
+// to 906 tokens as well: 626 instead of 601 us).  Ingests of 16 rows for 64 sequences, one over
+// 131000 positions and 63 over 512, with their first drafts and verification 3890 -> 1079 us
+// (chains of two, d 2560: 6571 -> 3712); with a longest context of 32768 3647 -> 2968, eight
+// prompts beside one such turn 1667 -> 1417.
 // Few tiles take pieces of one length whatever the context, and a captured pass those of the
 // contexts at hand (more of them, for the contexts it covers): a graph's launches and the same
 // calls one by one then sum in the same order, and give the same bits.  The pieces are longer
@@ -444,7 +445,7 @@ SplitPlan plan_row_splits(const osprey_handle* h, const SplitPlan& sp, int B, in
   const long work = tree ? sp.ctx_total * per_seq : sp.tile_ctx;
   // (an even deal, in the splits' whole lengths)
   const long even = work * c.n_kv_heads * 2 / (7L * h->n_cu) * sp.ctx / sp.ctx_max;
-  len = std::min(len, std::max(2 * even, 2 * kRowSplitLen));
+  len = std::min(len, std::max(4 * even, 2 * kRowSplitLen));
   len = std::max(len, (cover + max_split - 1) / max_split);
   len = (len + 63) / 64 * 64;
   SplitPlan p = sp;
