@@ -341,12 +341,14 @@ __global__ void __launch_bounds__(kSkThreads) k_skinny(GemvArgs a, int T, int kc
       }
 #pragma unroll
       for (int q = 0; q < AB; ++q) {
-        if (pr[q] < R && k0 + pc[q] < k_hi) {
+        if (pr[q] < R) {
           uint4 h, l;
           split_bf16x2(y[q][0], y[q][1], h.x, l.x);
           split_bf16x2(y[q][2], y[q][3], h.y, l.y);
           split_bf16x2(y[q][4], y[q][5], h.z, l.z);
           split_bf16x2(y[q][6], y[q][7], h.w, l.w);
+          // (the last unit's columns past the heads meet weights from clamped addresses)
+          if (k0 + pc[q] >= k_hi) h = l = make_uint4(0u, 0u, 0u, 0u);
           *reinterpret_cast<uint4*>(xh + pr[q] * PITCH + pc[q]) = h;
           *reinterpret_cast<uint4*>(xl + pr[q] * PITCH + pc[q]) = l;
         }

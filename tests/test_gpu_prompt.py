@@ -36,6 +36,11 @@ CASES = {
     "four_each_b66": ("p_qwen_small", [(b % 5, 4) for b in range(66)]),
     "odd_taps": ("p_odd_taps", [(5, 100), (0, 60)]),
     "wide_taps": ("p_wide_taps", [(0, 65), (3, 2), (64, 63)]),
+    # three and five query heads per kv head; widths that are no multiple of 256
+    "group3": ("p_group3", [(0, 70), (130, 45)]),
+    "group5_d320": ("p_group5_d320", [(0, 90), (31, 77)]),
+    "group5_d320_r80": ("p_group5_d320", [(3, 80)]),
+    "group5_d320_b70": ("p_group5_d320", [(b % 3, 1) for b in range(70)]),
     "f32": ("p_tiny_f32", [(0, 65)]),
     "f32_turn": ("p_tiny_f32", [(70, 3)]),
     # fp32 products go by groups of eight rows
@@ -57,6 +62,10 @@ def test_prompt_matches_oracle(name, K):
     # (taps of 3 x 200 columns: not a whole number of 32-column steps)
     if body == "p_odd_taps":
         w = synth.get("p_qwen_small").with_(target_hidden=200)
+    elif body == "p_group3":
+        w = synth.get("p_qwen_small").with_(n_q_heads=6)
+    elif body == "p_group5_d320":
+        w = synth.get("p_single64").with_(d_model=320, n_q_heads=5, n_kv_heads=1, d_ffn=448)
     elif body == "p_f32_two_layers":
         w = synth.get("p_tiny_f32").with_(n_layers=2)
     elif body.startswith("p_ffn"):
@@ -161,6 +170,43 @@ def test_tree_after_a_prompt_matches_oracle(rows):
     if gk != ok:
         near = parity.tree_near_tie_keys(t, 4.0 * err + 1e-9)
         assert parity.tree_mismatch_excused(gk, ok, near), (g_tok, t.tokens)
+
+
+@pytest.mark.parametrize("rows", [(100, 120), (20, 40), (300, 150)])
+def test_values_that_are_no_numbers_stay_in_their_sequence(rows):
+    """A prompt whose taps are NaN (and one with infinities) beside a sound one, whose cache
+    must come out bit for bit as without them."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_09338_amd import _lib as L
+    from paper_2609_09338_amd import workload as WL
+    from paper_2609_09338_amd.binding import Drafter, make_config
+    w = synth.get("p_qwen_small").with_(batch=3, n_layers=3)
+    dev, ns = "cuda:0", [rows[0], rows[1], rows[0]]
+    nb = max(ns) // 16 + 2
+    cfg = make_config(n_layers=w.n_layers, d_model=w.d_model, n_q_heads=w.n_q_heads, n_kv_heads=w.n_kv_heads,
+                      head_dim=w.head_dim, d_ffn=w.d_ffn, vocab_draft=w.vocab_draft, vocab_target=w.vocab_target,
+                      target_hidden=w.target_hidden, dtype=L.OSPREY_BF16, qk_norm=w.qk_norm, max_batch=3, max_k=1,
+                      max_seq_len=16 * nb, kv_num_blocks=3 * nb, max_new_rows=sum(ns))
+    dr = Drafter(cfg, {k: WL.to_dev(v, w, dev) for k, v in synth.make_weights(w).items()},
+                 torch.from_numpy(synth.make_d2t(w)).to(dev))
+    toks = torch.from_numpy(np.concatenate([synth.prompt_tokens(w, b, n) for b, n in enumerate(ns)])).to(dev)
+    got = []
+    for bad in (False, True):
+        taps = [WL.to_dev(synth.taps(w, 0, b, n), w, dev) for b, n in enumerate(ns)]
+        if bad:
+            taps[0][1:] = float("nan")
+            taps[2][::2] = float("inf")
+        for b in range(3):
+            dr.seq_reset(b, range(b * nb, (b + 1) * nb))
+        dr.kv.zero_()
+        print(f"[prompt] NaN {bad} rows {ns}", flush=True)
+        dr.draft_step([0, 1, 2], 0, torch.cat(taps), torch.zeros(3, device=dev), n_new=ns, new_tokens=toks)
+        torch.cuda.synchronize()
+        assert dr.device_errors() == 0
+        got.append(dr.kv.view(torch.int16).view(3, -1)[1].clone())
+    assert torch.equal(*got)
+    assert bool((got[0] != 0).any())
 
 
 def test_taps_past_two_gigabytes():
