@@ -299,7 +299,9 @@ __global__ void __launch_bounds__(256, 2) k_attn_rows(AttnArgs a, int n_tiles, i
 // Merge of a few splits for many rows: a wavefront per (row, head), lane l holding
 // HD / 64 dimensions of every split, the splits' loads four at a time.  (The general
 // merge kernel gives each (row, head) a block with slots for 64 splits: 81 us for two
-// splits of 1999 x 16 rows.)
+// splits of 1999 x 16 rows.)  Weights and sums are formed as where the O projection merges
+// (skinny.hip), in split order: a row's bits do not depend on which of the two merges it, nor
+// on how many splits past its own a pass is planned for.
 template <int HD>
 __global__ void __launch_bounds__(256) k_attn_join(AttnArgs a) {
   constexpr int DPL = HD / 64;
@@ -314,7 +316,11 @@ __global__ void __launch_bounds__(256) k_attn_join(AttnArgs a) {
   const float m = lane < ns ? ml.x : -INFINITY;
   const float M = wave_max(m);
   const float f = m > -INFINITY ? __expf(m - M) : 0.f;
-  const float L = wave_sum(lane < ns ? ml.y * f : 0.f);
+  float L = 0.f;
+  for (int sp = 0; sp < ns; ++sp) {
+    const float fs = lane_f(f, sp), ls = lane_f(ml.y, sp);
+    L = fs > 0.f ? L + ls * fs : L;
+  }
   const float w = L > 0.f ? f / L : 0.f;
   float y[DPL];
 #pragma unroll
@@ -328,8 +334,9 @@ __global__ void __launch_bounds__(256) k_attn_join(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float ws = s0 + i < ns ? lane_f(w, min(s0 + i, 63)) : 0.f;
+      const bool in = ws != 0.f;
 #pragma unroll
-      for (int e = 0; e < DPL; ++e) y[e] += s0 + i < ns ? v[i][e] * ws : 0.f;
+      for (int e = 0; e < DPL; ++e) y[e] = in ? y[e] + ws * v[i][e] : y[e];
     }
   }
   const long o = (long)r * a.nq * HD + h * HD + lane * DPL;

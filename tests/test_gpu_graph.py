@@ -50,7 +50,10 @@ def _reference(w, n_it):
 @pytest.mark.parametrize("name,change", [("p_qwen_small", {}), ("p_single128", {}), ("p_block", {}),
                                          ("p_qwen_small", dict(batch=12)), ("p_tiny_f32", dict(K=16)), ("p_block", dict(ctx_lo=1090, ctx_hi=1100)),
                                          ("p_single64", dict(ctx_lo=1100, ctx_hi=1100)),
-                                         ("p_block", dict(batch=1, ctx_lo=2040, ctx_hi=2040))])
+                                         ("p_block", dict(batch=1, ctx_lo=2040, ctx_hi=2040)),
+                                         # (merged by the O projection, by the merge kernel in the graph)
+                                         ("p_block", dict(batch=2, ctx_lo=990, ctx_hi=990)),
+                                         ("p_single64", dict(ctx_lo=100, ctx_hi=100))])
 def test_graph_replays_equal_stream_launches(name, change):
     _require_gpu()
     from paper_2609_09338_amd import workload as WL
